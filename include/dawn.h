@@ -74,16 +74,14 @@ typedef struct dawn_run_stats {
   int32_t levels;
   int32_t push_levels;        /* expansion steps run as push */
   int32_t pull_levels;        /* expansion steps run as pull */
-  int32_t launches;           /* traversal kernel launches (driver 3: those queued, some of
-                                 which may carry the final state only) */
+  int32_t launches;           /* traversal kernel launches */
   int64_t edges_examined;     /* adjacency entries read by expansion steps */
   int64_t source_edges;       /* sum over sources of sum of outdeg(u), u reached */
   int64_t reached;            /* sum over sources of reached nodes (sources included) */
   double kernel_ms;           /* device time of the traversal: HIP events around its kernels;
                                  dawn_sssp under driver 3 and for a source traversed by one
                                  workgroup (small_n): the GPU wall clock from the init
-                                 kernel's start to the point the end was found (launches
-                                 queued past the end are not counted) */
+                                 kernel's start to the end report */
   double total_ms;            /* host wall time of the call */
   /* dawn_sssp only, optional inputs: when frontier_sizes is non-null it receives
    * the number of nodes found at level L (L = 0 .. min(levels, frontier_cap) - 1)
@@ -104,24 +102,26 @@ typedef struct dawn_run_stats {
 typedef struct dawn_params {
   int32_t driver;             /* 1 persistent cooperative kernel (grid barrier per level),
                                  2 one launch per level with a host read-back,
-                                 3 level launches queued in batches (the first sized from the
-                                   graph's recent traversals, later ones `graph_levels`); the
-                                   call returns once the launch that finds the end has
-                                   reported to host memory, while launches queued past the
-                                   end (they only carry the final state) may still run on
-                                   the library's stream,
-                                 4 the same launches captured once in a HIP graph and replayed */
+                                 3 (default) one launch that runs every level, each on as many
+                                   workgroups as it can use (one; the first 32; all that
+                                   started), between an init launch and one that reports the
+                                   end to host memory; `block`, `big_degree`, `graph_levels`
+                                   and the medium_* knobs do not apply to it,
+                                 4 level launches captured once in a HIP graph and replayed,
+                                   `graph_levels` per host check */
   int32_t direction;          /* 1 push only, 2 pull only, 3 switch by alpha/beta */
   int32_t block;              /* threads per workgroup: 256, 512 or 1024 */
-  int32_t blocks_per_cu;      /* workgroups per compute unit of the persistent kernel and of
-                                 level launches (0: as many as a compute unit holds; level
+  int32_t blocks_per_cu;      /* workgroups per compute unit of the persistent kernel, of driver
+                                 3's launch and of level launches (0: as many as a compute unit
+                                 holds; driver 3's then has no more than a level of the graph
+                                 can use; level
                                  launches then use no more workgroups than a pull level has
                                  visited-bitmap words for, and at least one per compute unit) */
   int32_t big_degree;         /* push: out-degree at which a node's edges are spread over the grid */
   int32_t pull_lane_edges;    /* pull: in-edges one lane scans before its wave helps */
   float alpha;                /* switch push -> pull when frontier edges > unvisited edges / alpha */
   float beta;                 /* switch pull -> push when frontier nodes < n / beta */
-  int32_t graph_levels;       /* drivers 3, 4: level launches per host read-back (rounded up to even) */
+  int32_t graph_levels;       /* driver 4: level launches per host read-back (rounded up to even) */
   int32_t small_n;            /* a source whose weakly connected component has
                                  <= min(small_n, 2048) nodes is traversed by one workgroup
                                  (0 = never; not when direction forces pull; default 512:
@@ -142,11 +142,12 @@ typedef struct dawn_params {
   int32_t batch_sparse_words; /* batched push: a frontier node with at most this many nonzero
                                  64-lane words goes one edge per lane (1..4; default 4) */
   int32_t small_frontier_edges; /* single source, drivers 2-4: a push level whose frontier has
-                                 at most this many out-edges (and at most `block`) runs on one
-                                 workgroup, which also runs the small push levels after it in
-                                 the same launch with their frontiers in LDS
+                                 at most this many out-edges (and at most `block`; driver 3: at
+                                 most 1024) runs on one workgroup, which also runs the small
+                                 push levels after it in the same launch with their frontiers
+                                 in LDS
                                  (default 1024; -1: never) */
-  int32_t medium_edges;       /* single source, drivers 2-4: a push level whose frontier has
+  int32_t medium_edges;       /* single source, drivers 2 and 4: a push level whose frontier has
                                  more out-edges than such a one-workgroup level and at most
                                  this many runs on the first `medium_groups` workgroups of its
                                  launch, which also run the push levels after it that qualify,

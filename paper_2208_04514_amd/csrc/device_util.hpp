@@ -50,42 +50,71 @@ __device__ __forceinline__ u64 atom_or(u64* p, u64 v) {
   return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Inclusive prefix sum across the wave.
+// One step of a wave-wide scan: the value the DPP control fetches from another
+// lane, 0 where it fetches none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_get(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive prefix sum across the wave (every lane takes part): four shifts
+// within rows of 16 lanes, then the rows' totals broadcast to later rows.  Six
+// VALU instructions with no LDS in the chain; the same scan by six dependent
+// lane permutes takes about 0.2 us, and a level has several on its way.
 __device__ __forceinline__ int wave_incl_scan(int x) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int y = __shfl_up(x, d, kWave);
-    if (lane >= d) x += y;
-  }
+  x += dpp_get<0x111, 0xf>(x);   // row_shr:1
+  x += dpp_get<0x112, 0xf>(x);   // row_shr:2
+  x += dpp_get<0x114, 0xf>(x);   // row_shr:4
+  x += dpp_get<0x118, 0xf>(x);   // row_shr:8
+  x += dpp_get<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  x += dpp_get<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
   return x;
 }
 
-__device__ __forceinline__ unsigned wave_sum(unsigned x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
+// Inclusive prefix maximum across the wave of values >= 0.
+__device__ __forceinline__ int wave_incl_max(int x) {
+  x = max(x, dpp_get<0x111, 0xf>(x));
+  x = max(x, dpp_get<0x112, 0xf>(x));
+  x = max(x, dpp_get<0x114, 0xf>(x));
+  x = max(x, dpp_get<0x118, 0xf>(x));
+  x = max(x, dpp_get<0x142, 0xa>(x));
+  x = max(x, dpp_get<0x143, 0xc>(x));
   return x;
+}
+
+// Sums across the wave (every lane takes part), the same in every lane.
+__device__ __forceinline__ unsigned wave_sum(unsigned x) {
+  return (unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)x), kWave - 1);
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u64 dpp_get64(u64 x) {
+  const unsigned lo = (unsigned)dpp_get<CTRL, ROWS>((int)(unsigned)x);
+  const unsigned hi = (unsigned)dpp_get<CTRL, ROWS>((int)(unsigned)(x >> 32));
+  return ((u64)hi << 32) | lo;
 }
 
 __device__ __forceinline__ u64 wave_sum(u64 x) {
-  unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    unsigned olo = __shfl_xor(lo, d, kWave), ohi = __shfl_xor(hi, d, kWave);
-    unsigned nlo = lo + olo;
-    hi = hi + ohi + (nlo < lo ? 1u : 0u);
-    lo = nlo;
-  }
+  x += dpp_get64<0x111, 0xf>(x);
+  x += dpp_get64<0x112, 0xf>(x);
+  x += dpp_get64<0x114, 0xf>(x);
+  x += dpp_get64<0x118, 0xf>(x);
+  x += dpp_get64<0x142, 0xa>(x);
+  x += dpp_get64<0x143, 0xc>(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, kWave - 1);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), kWave - 1);
   return ((u64)hi << 32) | lo;
 }
 
 __device__ __forceinline__ u64 wave_or(u64 x) {
-  unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    lo |= __shfl_xor(lo, d, kWave);
-    hi |= __shfl_xor(hi, d, kWave);
-  }
+  x |= dpp_get64<0x111, 0xf>(x);
+  x |= dpp_get64<0x112, 0xf>(x);
+  x |= dpp_get64<0x114, 0xf>(x);
+  x |= dpp_get64<0x118, 0xf>(x);
+  x |= dpp_get64<0x142, 0xa>(x);
+  x |= dpp_get64<0x143, 0xc>(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, kWave - 1);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), kWave - 1);
   return ((u64)hi << 32) | lo;
 }
 

@@ -183,6 +183,67 @@ struct SsspArgs {
                               //   null otherwise
 };
 
+// ------------------------------------------ single-source sessions --
+// (session.hip: all levels of a traversal in one launch)
+constexpr int kSessGroups = 32;       // barrier groups at most
+constexpr int kSessGroup = 32;        // workgroups (consecutive ranks) per group
+constexpr int kSessStripes = 8;       // sub-queues of a frontier
+constexpr int kSessSegs = kSessGroup + 1;   // segments of a frontier's queue at most
+constexpr int kSessRec = 64;          // words of a level record
+constexpr int kPiece = 2048;          // edges per queue entry: longer rows take several
+constexpr int kSessPerCu = 4;         // workgroups per compute unit
+constexpr unsigned long long kJoinTicks = 500;   // 100 MHz ticks the member list stays open
+
+// A barrier group's counters of one level: nodes found, their out-edges,
+// adjacency entries examined, each with the arrivals in its top 16 bits (the
+// sums stay below 2^31).
+struct alignas(kLine) SessGroupLine {
+  u64 w[3];
+};
+struct alignas(kLine) SessStripe {
+  unsigned n;
+};
+struct alignas(kLine) SessWord {
+  u64 w;
+};
+// A cluster member's report of one level, each word tagged with the level:
+// entries, nodes found, their out-edges, adjacency entries examined.
+struct alignas(kLine) SessReport {
+  u64 w[4];
+};
+// Counters of one grid level; three, used in turn.
+struct SessSlot {
+  SessGroupLine grp[kSessGroups];
+  SessStripe q[kSessStripes];         // entries of the next frontier's sub-queues
+};
+struct SessCtrl {
+  SessSlot slot[3];
+  SessWord joined[kSessGroups];       // bit per workgroup that has started
+  alignas(kLine) unsigned memb[kSessGroups];   // those in the session
+  alignas(kLine) u64 rec[kSessRec];   // the level record (tag in the high half)
+  SessReport crec[2][kSessGroup];     // cluster levels, by level parity: each member's line
+  SessStripe over[3];                 // cluster levels, by level % 3: entries past a segment
+};
+struct SessArgs {
+  SessCtrl* sc;
+  // frontier entries (row start, degree) by queue parity.  Grid levels:
+  // kSessStripes sub-queues of qcap entries; cluster levels: kSessGroup
+  // segments of ccap entries, then one of all the rest
+  u64* q[2];
+  unsigned qcap, ccap;
+  int32_t source;
+};
+// A level's rows cut into pieces: at most one partial piece per node.
+inline size_t sess_queue_cap(int32_t n, long long m) {
+  return (size_t)n + (size_t)(m / kPiece) + 64;
+}
+// A cluster segment: the segments together take at most 7 of the 8 sub-queues'
+// room, so that the rest holds any level's entries.
+inline size_t sess_cluster_cap(size_t qcap) {
+  const size_t fit = (kSessStripes - 1) * qcap / kSessGroup;
+  return fit < 2048 ? fit : 2048;
+}
+
 // ----------------------------------------------------------- host objects --
 struct Ctx;
 struct GraphRec;
@@ -209,6 +270,7 @@ struct SsspWs {
   int32_t* cu[2] = {nullptr, nullptr};
   int32_t* ck[2] = {nullptr, nullptr};
   SsspCtrl* ctrl = nullptr;
+  SessCtrl* sess = nullptr;     // behind ctrl in the same allocation
   int32_t* dist = nullptr;      // internal output for host-destination calls
   int32_t* level_nf = nullptr;
   uint8_t* level_dir = nullptr;
@@ -320,6 +382,9 @@ dawn_status graph_wcc(Ctx* ctx, GraphRec* g, hipStream_t stream);
 // sssp.hip
 dawn_status sssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, int32_t source,
                      int32_t* dist, bool device_out, dawn_run_stats* stats);
+// session.hip: queue a traversal's launches (init, session, end report)
+dawn_status sess_launch(Ctx* ctx, const SsspArgs& a, const SessArgs& x, int blocks_per_cu,
+                        hipStream_t s);
 // The no-allocation variant: buffers from the file-scope scratch array of
 // sssp.hip, whose per-device address scratch_init (device current) looks up.
 dawn_status scratch_init(int device);

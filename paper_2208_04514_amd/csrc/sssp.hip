@@ -38,7 +38,9 @@
 //
 // Drivers: (1) one persistent cooperative kernel with a software grid barrier
 // between levels, (2) one kernel per level with the counters read back by the
-// host, (3) a HIP graph of level kernels replayed until a device flag says done.
+// host, (3, the default) one launch that runs every level on as many
+// workgroups as it can use (session.hip), (4) a HIP graph of level kernels
+// replayed until a device flag says done.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -50,6 +52,7 @@
 
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "sssp_dev.hpp"
 
 namespace dawn {
 
@@ -472,12 +475,6 @@ __device__ __forceinline__ void finish_level(const SsspArgs& a, int L, Counters&
   c.edges = 0;
 }
 
-struct SlotSum {
-  unsigned nf;
-  u64 mf;
-  u64 edges;
-};
-
 __device__ __forceinline__ SlotSum sum_slot(const LevelSlot* s) {
   SlotSum r{0, 0, 0};
   for (int i = 0; i < kStripes; ++i) {
@@ -507,45 +504,6 @@ __device__ __forceinline__ void zero_slot(LevelSlot* s, int tid, int nthreads) {
     const int words = (int)(sizeof(LevelSlot) / 4);
     for (int i = tid; i < words; i += nthreads) w[i] = 0;
   }
-}
-
-// Fold level st.level's counters into the state and choose level st.level+1.
-// Direction switch in the style of direction-optimising BFS: go bottom-up
-// (pull) when the frontier's out-edges exceed the unvisited out-edges / alpha
-// while the frontier grows, and back top-down (push) when the frontier falls
-// under n / beta while it shrinks.
-__device__ void decide(const SsspArgs& a, LevelState& st, const SlotSum& sl, bool record) {
-  const int L = st.level;
-  if (sl.nf > 0) st.last_nonempty = L;
-  st.mu -= (long long)sl.mf;
-  st.edges_total += sl.edges;
-  st.source_edges += sl.mf;
-  st.reached += sl.nf;
-  if (record && L < a.lrec) a.level_nf[L] = (int32_t)sl.nf;
-  const unsigned prev = st.prev_nf;
-  st.prev_nf = sl.nf;
-  if (sl.mf == 0) {
-    st.done = 1;
-    return;
-  }
-  if (L + 1 > a.n) {
-    st.done = 2;
-    return;
-  }
-  bool pull = st.pull;
-  if (a.mode == 1) {
-    pull = false;
-  } else if (a.mode == 2) {
-    pull = true;
-  } else if (!pull) {
-    if ((double)sl.mf * (double)a.alpha > (double)st.mu && sl.nf > prev) pull = true;
-  } else {
-    if ((double)sl.nf * (double)a.beta < (double)a.n && sl.nf < prev) pull = false;
-  }
-  st.pull = pull ? 1 : 0;
-  st.level = L + 1;
-  if (pull) st.pull_levels++; else st.push_levels++;
-  if (record && st.level < a.lrec) a.level_dir[st.level] = pull ? 2 : 1;
 }
 
 // Seed the source (one thread; slots 1 and 2 are zeroed by the caller).
@@ -639,25 +597,6 @@ __global__ __launch_bounds__(BLOCK) void sssp_persistent(SsspArgs a0) {
     if (!grid_sync(&a.ctrl->bar)) return;
   }
   if (leader) a.ctrl->st[1] = st;
-}
-
-// The state a launch of parity `parity` leaves, to the host mirror (one
-// thread).  `ended`: this launch found the end of the traversal, so the end
-// stamp and tag follow, the tag ordered after the rest by a system-scope
-// release, which also writes back this XCD's L2: the host returns on the tag
-// and its caller may read the distances at once.  Distances stored by other
-// waves of the workgroup must be complete before (their waves wait for
-// their stores ahead of the barrier that precedes the report); those of
-// earlier launches were written back when those launches ended.
-__device__ __forceinline__ void report(const SsspArgs& a, int parity, const LevelState& s,
-                                       bool ended) {
-  if (!a.hm) return;
-  a.hm->st[parity] = s;
-  if (ended) {
-    a.hm->t_end = wall_clock64();
-    __hip_atomic_store(&a.hm->end_tag, (a.seq << 1) | (unsigned)parity, __ATOMIC_RELEASE,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
-  }
 }
 
 // ------------------------------------------------- one-workgroup traversal --
@@ -1444,18 +1383,24 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out
   dawn_status s = DAWN_OK;
   for (int i = 0; i < 2 && s == DAWN_OK; ++i) {
     if ((s = alloc((void**)&w->vis[i], nw * 8 + 256)) != DAWN_OK) break;
-    if ((s = alloc((void**)&w->qs[i], (size_t)kStripes * n * 4 + 256)) != DAWN_OK) break;
+    // (the level kernel's sub-queues, or a session's)
+    if ((s = alloc((void**)&w->qs[i],
+                   std::max((size_t)kStripes * n * 4 + 256,
+                            (size_t)kSessStripes * sess_queue_cap(n, g->m) * 8))) != DAWN_OK)
+      break;
     if ((s = alloc((void**)&w->cu[i], chunk_cap * 4)) != DAWN_OK) break;
     if ((s = alloc((void**)&w->ck[i], chunk_cap * 4)) != DAWN_OK) break;
   }
-  if (s == DAWN_OK) s = alloc((void**)&w->ctrl, sizeof(SsspCtrl));
+  constexpr size_t ctrl_bytes = (sizeof(SsspCtrl) + kLine - 1) / kLine * kLine;
+  if (s == DAWN_OK) s = alloc((void**)&w->ctrl, ctrl_bytes + sizeof(SessCtrl));
   if (s == DAWN_OK) s = alloc((void**)&w->dist, (size_t)n * 4);
   if (s == DAWN_OK) s = alloc((void**)&w->level_nf, (size_t)w->lrec * 4);
   if (s == DAWN_OK) s = alloc((void**)&w->level_dir, (size_t)w->lrec);
 
   // the destructor frees each buffer and returns `bytes` to the budget at once
   if (s != DAWN_OK) return s;
-  DAWN_HIP(hipMemset(w->ctrl, 0, sizeof(SsspCtrl)));
+  DAWN_HIP(hipMemset(w->ctrl, 0, ctrl_bytes + sizeof(SessCtrl)));
+  w->sess = reinterpret_cast<SessCtrl*>(reinterpret_cast<char*>(w->ctrl) + ctrl_bytes);
   DAWN_HIP(hipHostMalloc((void**)&w->h_ctrl, sizeof(SsspCtrl), hipHostMallocDefault));
   DAWN_HIP(hipHostMalloc((void**)&w->h_m, sizeof(HostMirror),
                          hipHostMallocCoherent | hipHostMallocMapped));
@@ -1574,10 +1519,29 @@ static dawn_status wait_end(SsspWs* w, unsigned seq, int* parity) {
   }
 }
 
-// Direct-launch driver: level launches queued beyond what the graph's recent
-// traversals needed (with none, R-MAT 20 calls ran out of launches often
-// enough to cost 25 us per call on average).
-constexpr int kSpareLaunches = 1;
+// One-launch driver: every level runs in the session kernel; the host waits
+// for the end report of the launch after it.
+static dawn_status run_session(Ctx* ctx, SsspWs* w, const SsspArgs& a0, int blocks_per_cu,
+                               int32_t* d_dist, int source, int* launches, int* final_parity) {
+  SsspArgs a = a0;
+  a.dist = d_dist;
+  a.seq = next_seq(w);
+  SessArgs x;
+  x.sc = w->sess;
+  x.q[0] = reinterpret_cast<u64*>(w->qs[0]);
+  x.q[1] = reinterpret_cast<u64*>(w->qs[1]);
+  x.qcap = (unsigned)sess_queue_cap(a.n, a.m);
+  x.ccap = (unsigned)sess_cluster_cap(x.qcap);
+  x.source = source;
+  DAWN_TRY(sess_launch(ctx, a, x, blocks_per_cu, w->stream));
+  DAWN_HIP(hipEventRecord(w->ev1, w->stream));
+  int parity = -1;
+  DAWN_TRY(wait_end(w, a.seq, &parity));
+  if (parity < 0) return fail(DAWN_E_DEVICE, "traversal ended without a report");
+  *launches = 3;
+  *final_parity = parity;
+  return DAWN_OK;
+}
 
 template <int BLOCK>
 static dawn_status run_levels(Ctx* ctx, GraphRec* g, SsspWs* w, const SsspArgs& a, int grid,
@@ -1655,47 +1619,6 @@ static dawn_status run_levels(Ctx* ctx, GraphRec* g, SsspWs* w, const SsspArgs& 
     return fail(DAWN_E_DEVICE, "level loop did not terminate");
   }
   graph_levels += graph_levels & 1;
-  if (driver == 3) {
-    // K level launches queued per host check.  The first batch covers what
-    // the graph's recent traversals needed (one more than their level
-    // launches, for the launch that sees the end), so a typical traversal
-    // costs one batch and few launches past its end; a launch after the end
-    // only carries the final state along.  The host waits for the end tag in
-    // the host mirror, not for the stream: it returns as soon as the launch
-    // that found the end has reported (every level's writes are complete by
-    // then, the launches being stream-ordered), and the launches still queued
-    // behind it overlap with what the caller does next.  The stream is waited
-    // on only when a batch has run out without the end.
-    SsspArgs ad = a;
-    ad.seq = next_seq(w);
-    hipLaunchKernelGGL(sssp_init<BLOCK>, dim3(fill_grid), dim3(BLOCK), 0, w->stream, ad, d_dist,
-                       source);
-    *launches = 1;
-    const int hint = g->launch_hint.load(std::memory_order_relaxed);
-    int batch = hint > 0 ? std::min(hint + kSpareLaunches, graph_levels * 4) : graph_levels;
-    long long queued = 0;
-    while (queued <= max_launch) {
-      for (int i = 0; i < batch; ++i)
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), shmem, w->stream, ad,
-                           (int)((queued + i) & 1));
-      DAWN_HIP(hipGetLastError());
-      *launches += batch;
-      queued += batch;
-      DAWN_HIP(hipEventRecord(w->ev1, w->stream));
-      int parity = -1;
-      DAWN_TRY(wait_end(w, ad.seq, &parity));
-      if (parity >= 0) {
-        // launches this traversal needed: every one up to the one that
-        // found the end
-        const int need = w->h_m->st[parity].launches;
-        g->launch_hint.store(std::max(need, hint - 1), std::memory_order_relaxed);
-        *final_parity = parity;
-        return DAWN_OK;
-      }
-      batch = graph_levels;
-    }
-    return fail(DAWN_E_DEVICE, "level loop did not terminate");
-  }
   // driver 4: one HIP graph holds the init kernel and an even number of level
   // launches (parities 0, 1, 0, 1, ...); a second graph of level launches
   // alone continues a traversal that needs more levels
@@ -1811,6 +1734,8 @@ static dawn_status sssp_dispatch(Ctx* ctx, GraphRec* g, SsspWs* w, const dawn_pa
     *final_parity = 1;
     return launch_persistent<BLOCK>(ctx, w, a, p.blocks_per_cu, false);
   }
+  if (p.driver == 3)
+    return run_session(ctx, w, a, p.blocks_per_cu, d_dist, source, launches, final_parity);
   // the shape depends on the graph, block size and kernel variant only:
   // found once per workspace, block size and variant
   const int bi = (BLOCK == 256 ? 0 : BLOCK == 512 ? 1 : 2) * 2 + (a.medium_edges > 0 ? 1 : 0);
