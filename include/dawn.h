@@ -213,7 +213,8 @@ dawn_status dawn_graph_get_info(dawn_ctx *ctx, int32_t graph, dawn_graph_info *o
 
 /* Attach non-negative integer edge weights to a resident graph (copied:
  * weights[e], host, m int32, belongs to CSR entry e, the edge from e's row to
- * col[e]).  A second call replaces them.  Every path length must fit an int32
+ * col[e]; with room to spare in the budget a second copy of the rows is kept,
+ * ordered for the rounds).  A second call replaces them.  Every path length must fit an int32
  * distance: max weight x (n - 1) <= 2^31 - 2.  Used by dawn_sssp_weighted
  * only.  Errors: INVALID_ARG (null, negative or too large weights),
  * NOT_FOUND, NO_MEMORY, DEVICE. */
@@ -237,10 +238,10 @@ dawn_status dawn_sssp(dawn_ctx *ctx, int32_t graph, int32_t source, int32_t *dis
  * (min, +) semiring, which Section 5 names as future work.  dist[v] is the
  * least sum of weights over directed paths source -> v (int32, -1 when no
  * path exists), for the weights of dawn_graph_set_weights.  Each round
- * relaxes the out-edges of the nodes whose distance dropped in the previous
- * round (an atomic minimum per edge) until a round lowers nothing; a node may
- * join several rounds, so stats->levels counts rounds, which can exceed the
- * hop depth.  dist: n int32 (host, or device with DAWN_DEVICE_OUT); stats may
+ * relaxes out-edges of the nodes whose distance dropped in the previous round
+ * (an atomic minimum per edge), nearest distances first, until nothing drops;
+ * a node may join several rounds, so stats->levels counts rounds, which can
+ * exceed the hop depth.  dist: n int32 (host, or device with DAWN_DEVICE_OUT); stats may
  * be NULL (edges_examined is not counted; source_edges and reached are as
  * for dawn_sssp).  Errors: INVALID_ARG (also: no weights attached),
  * NOT_FOUND, NO_MEMORY, DEVICE. */

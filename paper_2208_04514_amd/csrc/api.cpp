@@ -311,7 +311,9 @@ dawn_status dawn_graph_set_weights(dawn_ctx* c, int32_t graph, const int32_t* we
   DAWN_TRY(get_graph(ctx, graph, &g));
   if (!weights && g->m > 0) return fail(DAWN_E_INVALID_ARG, "null weights");
   int32_t mx = 0;
+  long long sum = 0;
   for (long long e = 0; e < g->m; ++e) {
+    sum += weights[e];
     if (weights[e] < 0) return fail(DAWN_E_INVALID_ARG, "weights[%lld] = %d is negative", e, weights[e]);
     mx = std::max(mx, weights[e]);
   }
@@ -329,11 +331,23 @@ dawn_status dawn_graph_set_weights(dawn_ctx* c, int32_t graph, const int32_t* we
     dev_free(ctx, d, bytes);
     return fail(DAWN_E_DEVICE, "weights upload: %s", hipGetErrorString(e));
   }
+  WeightRows rows;
+  dawn_status st = wsssp_layout(ctx, g.get(), d, mx, g->m > 0 ? (double)sum / (double)g->m : 0.0,
+                                &rows);
+  if (st != DAWN_OK) {
+    dev_free(ctx, d, bytes);
+    return st;
+  }
   std::lock_guard<std::mutex> lk(g->mu);
-  if (g->wt) dev_free(ctx, g->wt, bytes);
-  else g->bytes += bytes;
+  g->bytes += bytes * (rows.light ? 3 : 1) + (rows.light ? (size_t)g->n * 4 : 0);
+  if (g->wt) g->bytes -= bytes * (g->w_light ? 3 : 1) + (g->w_light ? (size_t)g->n * 4 : 0);
+  wsssp_weights_free(g.get());
   g->wt = d;
   g->max_w = mx;
+  g->w_col = rows.col;
+  g->w_wt = rows.wt;
+  g->w_light = rows.light;
+  g->w_delta = rows.delta;
   return DAWN_OK;
 }
 

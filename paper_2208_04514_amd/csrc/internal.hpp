@@ -187,10 +187,10 @@ struct SsspArgs {
 // (session.hip: all levels of a traversal in one launch)
 constexpr int kSessGroups = 32;       // barrier groups at most
 constexpr int kSessGroup = 32;        // workgroups (consecutive ranks) per group
-constexpr int kSessStripes = 8;       // sub-queues of a frontier
+constexpr int kSessStripes = 4;       // sub-queues of a frontier
 constexpr int kSessSegs = kSessGroup + 1;   // segments of a frontier's queue at most
 constexpr int kSessRec = 64;          // words of a level record
-constexpr int kPiece = 2048;          // edges per queue entry: longer rows take several
+constexpr int kPiece = 64;           // edges per queue entry: longer rows take several
 constexpr int kSessPerCu = 4;         // workgroups per compute unit
 constexpr unsigned long long kJoinTicks = 500;   // 100 MHz ticks the member list stays open
 
@@ -233,10 +233,18 @@ struct SessArgs {
   unsigned qcap, ccap;
   int32_t source;
 };
-// A level's rows cut into pieces: at most one partial piece per node.
-inline size_t sess_queue_cap(int32_t n, long long m) {
-  return (size_t)n + (size_t)(m / kPiece) + 64;
+// A level's rows cut into pieces of `piece` edges: at most one partial piece per
+// node.
+inline size_t sess_queue_cap(int32_t n, long long m, int piece) {
+  return (size_t)n + (size_t)(m / piece) + 64;
 }
+// Edges per queue entry, longer rows taking several.  A group of 64 entries is
+// one wave's, so the piece bounds how uneven the waves' shares are; writing
+// pieces costs too.  Hops push large frontiers of long rows only when told to
+// (R-MAT 20 x 16: 1.51 ms with 2048 edges, 1.56 with 256, 1.63 with 64);
+// weighted rounds always do (R-MAT 20 x 4: 10.2 ms with 256, 5.7 with 64).
+constexpr int kHopPiece = 1024;
+constexpr int kWeightPiece = 64;
 // A cluster segment: the segments together take at most 7 of the 8 sub-queues'
 // room, so that the rest holds any level's entries.
 inline size_t sess_cluster_cap(size_t qcap) {
@@ -337,7 +345,12 @@ struct GraphRec {
   // weighted graphs (dawn_graph_set_weights): weight of each CSR entry
   int32_t* wt = nullptr;
   int32_t max_w = 0;
-  std::atomic<int> wsssp_hint{0};         // rounds the last weighted run needed
+  // the rows with the edges lighter than w_delta first, and how many those are
+  // (null: no such copy)
+  int32_t* w_col = nullptr;
+  int32_t* w_wt = nullptr;
+  int32_t* w_light = nullptr;
+  int32_t w_delta = 1;
   void* wpool = nullptr;                  // pooled weighted-run workspaces (wsssp.hip)
   // device staging of host-destination batched rows, kept between calls
   int32_t* stage = nullptr;
@@ -395,6 +408,14 @@ dawn_status sssp_run_noalloc(Ctx* ctx, GraphRec* g, const dawn_params& p, int32_
 dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool device_out,
                       dawn_run_stats* stats);
 void wsssp_pool_free(GraphRec* g);
+// Bucket width for these weights and the rows laid out for it (device).
+struct WeightRows {
+  int32_t delta;
+  int32_t *col, *wt, *light;
+};
+dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, int32_t* wt, int32_t max_w, double mean_w,
+                         WeightRows* out);
+void wsssp_weights_free(GraphRec* g);
 
 // mssp.hip
 dawn_status mssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, const int32_t* sources,

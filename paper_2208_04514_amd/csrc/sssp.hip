@@ -1386,7 +1386,7 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out
     // (the level kernel's sub-queues, or a session's)
     if ((s = alloc((void**)&w->qs[i],
                    std::max((size_t)kStripes * n * 4 + 256,
-                            (size_t)kSessStripes * sess_queue_cap(n, g->m) * 8))) != DAWN_OK)
+                            (size_t)kSessStripes * sess_queue_cap(n, g->m, kHopPiece) * 8))) != DAWN_OK)
       break;
     if ((s = alloc((void**)&w->cu[i], chunk_cap * 4)) != DAWN_OK) break;
     if ((s = alloc((void**)&w->ck[i], chunk_cap * 4)) != DAWN_OK) break;
@@ -1530,7 +1530,7 @@ static dawn_status run_session(Ctx* ctx, SsspWs* w, const SsspArgs& a0, int bloc
   x.sc = w->sess;
   x.q[0] = reinterpret_cast<u64*>(w->qs[0]);
   x.q[1] = reinterpret_cast<u64*>(w->qs[1]);
-  x.qcap = (unsigned)sess_queue_cap(a.n, a.m);
+  x.qcap = (unsigned)sess_queue_cap(a.n, a.m, kHopPiece);
   x.ccap = (unsigned)sess_cluster_cap(x.qcap);
   x.source = source;
   DAWN_TRY(sess_launch(ctx, a, x, blocks_per_cu, w->stream));

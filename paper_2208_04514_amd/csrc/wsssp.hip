@@ -14,23 +14,38 @@
 // relaxed again whenever its distance drops).  Unlike the Boolean loop a
 // node may join several frontiers, so rounds can outnumber BFS levels.
 //
+// Order.  Relaxing in hop order alone relaxes an edge again whenever its source
+// improves: 3 times on R-MAT 20, 7 on a road-like grid (weights 1..100).  So
+// distances are settled in buckets of width delta, the near-far form of
+// delta-stepping (Meyer and Sanders): only nodes below the bucket's bound T join
+// the frontier; when it is empty every distance below T is final, and one pass
+// over the distances collects the next bucket's nodes.  With delta below the
+// largest weight (`split`), a round also leaves alone the edges that reach past
+// T, and they are relaxed once, from the settled distances, when the bucket is
+// done.  For that the weights come with a copy of the rows whose edges lighter
+// than delta stand first: a round looks at those alone.  The settled nodes have
+// a bitmap, which most targets of the later pass are found in (it stays in the
+// caches; distances at random do not).  An empty bucket doubles the width until
+// a node is found.
+//
+// delta = kDelta x mean weight / mean out-degree: the denser the graph, the
+// more often an unsettled node's row is relaxed in vain, the sparser, the fewer
+// nodes a round has to work on.
+//
+// Bound: on R-MAT 20 the rounds over hubs' rows (random distances, several
+// dependent accesses an edge: 30 to 120 G edges/s), on grids the levels' chains
+// (5 to 8 us each).  Per source (MI355X, weights 1..100), hop order with a
+// launch per round -> now: R-MAT 20 1.78 -> 1.13 ms, grid 1024^2 4.6 -> 1.7 ms.
+//
 // Distances are int32 with -1 for "unreached": compared as unsigned, -1 is
 // the largest value, so the atomic minimum needs no sentinel pass.  The
 // upload of the weights checks that every path length fits (max weight x
 // (n - 1) < 2^31 - 1).
 //
-// Work per round (64-wide waves): frontier nodes of out-degree below
-// kWBig are taken 64 per wave from the queue and the wave walks the union of
-// their out-lists four edges per lane and step (owner found by a binary
-// search over the wave's prefix sums); larger rows are cut into chunks of
-// kWChunk edges listed when the node joins the frontier and spread over the
-// waves.  A node joins the next frontier once per round: its bit in the next
-// round's membership bitmap is set with an atomic OR, and the claimer stages
-// it in its wave's LDS buffer; full buffers go to one of kStripes
-// sub-queues with one counter atomic each (the L2 performs atomics one line
-// at a time, so every stripe's counter owns a line).  Each round clears the
-// bits of the frontier it consumes, so the bitmap of parity p is clear again
-// when it is next written.
+// All rounds run in one launch (session_dev.hpp).  A node joins the next
+// frontier once per round: its bit in the next round's membership bitmap is
+// set with an atomic OR, and each round clears the bits of the frontier it
+// consumes, so the bitmap of parity p is clear again when it is next written.
 #include <string.h>
 
 #include <algorithm>
@@ -38,35 +53,36 @@
 
 #include "device_util.hpp"
 #include "internal.hpp"
+#include "session_dev.hpp"
 
 namespace dawn {
 
-constexpr int kWBlock = 256;
-constexpr int kWBig = 256;      // out-degree from which a frontier node's row goes by chunks
-constexpr int kWChunk = 256;    // edges per chunk (four per lane of a wave)
+// Bucket width, measured at 8, 16, 32 and 64 (ms, 4 sources R-MAT 20: 4.51,
+// 4.52, 5.85, 7.45; 2 sources grid 1024^2: 4.44, 3.68, 3.38, 3.34; a smaller
+// grid 2.04, 1.82, 1.85, 1.95): the narrower where the light rows pay (split).
+constexpr double kDelta = 16.0;
+constexpr double kDeltaWhole = 32.0;
+// A bucket whose nodes have fewer out-edges than this takes some 25 us whatever
+// it holds: the next is twice as wide.
+constexpr unsigned kSmallBucket = 1 << 19;
 
-// Counters of one round's output (a ring of three, indexed round % 3: round
-// r reads slot r % 3, appends to (r + 1) % 3 and clears (r + 2) % 3).
-struct alignas(kLine) WStripe {
-  unsigned qn;                  // entries of this stripe's sub-queue
-};
-
-struct WSlot {
-  WStripe s[kStripes];
-  alignas(kLine) unsigned cn;   // chunks of big-degree nodes
-};
-
-struct alignas(kLine) WRun {
-  int done;                     // 1: a round found its frontier empty; 2: watchdog
-  int last_round;               // that round
-  // the closing reduction, striped over lines: [s][0] reached nodes, [s][1]
-  // the sum of their out-degrees
-  alignas(kLine) u64 part[kStripes][kLine / 8];
+// What a weighted run leaves for the host (coherent host memory).
+struct WMirror {
+  unsigned rounds, done;
+  unsigned long long reached, source_edges;
+  unsigned long long t_start, t_end;
+  unsigned end_tag;
 };
 
 struct WCtrl {
-  WSlot slot[3];
-  WRun run;
+  SessCtrl sess;
+  alignas(kLine) unsigned done;         // 1 finished, 2 watchdog
+  unsigned rounds;
+  // the closing reduction, a line per stripe: reached nodes, their out-degrees
+  struct alignas(kLine) Part {
+    u64 reached, edges;
+  } part[kStripes];
+  alignas(kLine) unsigned closed;       // workgroups that have added theirs
 };
 
 struct WArgs {
@@ -75,13 +91,18 @@ struct WArgs {
   const int32_t* rp;
   const int32_t* col;
   const int32_t* wt;            // weight of each CSR entry
+  const int32_t* light;         // split: a row's edges lighter than delta stand first, this
+                                //   many of them (null: rows as uploaded)
   int32_t* dist;                // output (device)
-  int32_t* q[2];                // frontier queues by round parity: kStripes sub-queues
-                                //   of n entries each
-  int32_t* cu[2];               // chunk lists: node
-  int32_t* ck[2];               //              chunk index within its row
-  u64* inq[2];                  // frontier membership bitmaps by parity
+  u64* fin;                     // split: nodes of finished buckets
+  u64* inq[2];                  // frontier membership bitmaps by round parity
   WCtrl* ctrl;
+  WMirror* hm;
+  unsigned seq;
+  unsigned delta;               // bucket width
+  int32_t split;                // delta < largest weight: edges past the bound wait
+  unsigned half;                // half the graph's edges
+  unsigned max_rounds;
 };
 
 __device__ __forceinline__ unsigned umin_atomic(int32_t* p, unsigned v) {
@@ -89,223 +110,367 @@ __device__ __forceinline__ unsigned umin_atomic(int32_t* p, unsigned v) {
                                 __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kWWaveBuf = 256;   // entries a wave stages before one reserving atomic
+constexpr unsigned kUnreached = ~0u;
+constexpr unsigned kWhole = ~0u;        // piece number of an uncut row
 
-struct WQueue {
-  int32_t* buf;                 // this wave's LDS staging area
-  int cnt;                      // wave-uniform fill
+// What a level of the session does.
+enum WPhase {
+  kNear = 0,        // relax the frontier's rows; targets below the bound join the next
+  kSettled = 1,     // collect the bucket's nodes
+  kHeavy = 2,       // relax their edges that reach the bound or past it
+  kCollect = 3      // collect the nodes of the next bucket
 };
 
-// The wave's staged entries to its stripe's sub-queue of round r + 1.
-__device__ __forceinline__ void wq_flush(const WArgs& a, int r, WQueue& q) {
-  if (q.cnt == 0) return;
-  const int stripe = blockIdx.x % kStripes;
-  unsigned base = 0;
-  if (lane_id() == 0) base = atom_add(&a.ctrl->slot[(r + 1) % 3].s[stripe].qn, (unsigned)q.cnt);
-  base = (unsigned)__shfl((int)base, 0, kWave);
-  int32_t* dst = a.q[(r + 1) & 1] + (size_t)stripe * (size_t)a.n + base;
-  __builtin_amdgcn_wave_barrier();
-  for (int i = lane_id(); i < q.cnt; i += kWave) dst[i] = q.buf[i];
-  __builtin_amdgcn_wave_barrier();
-  q.cnt = 0;
-}
+// Queue entries are (node, piece of its row).
+struct WeightPolicy {
+  static constexpr int kPiece = kWeightPiece;
+  using Args = WArgs;
+  struct State {
+    unsigned phase, par;        // par: membership bitmap of the frontier
+    unsigned lo, hi;            // the bucket: distances in [lo, hi)
+    unsigned width;             // of the next collection
+    unsigned rounds;            // near rounds run
+    unsigned beyond;            // reached nodes past the bucket at its collection
+    unsigned settled;           // out-edges of the finished buckets
+    unsigned steps;
+  };
+  using Shared = SessShared<WeightPolicy>;
 
-// v's distance dropped in round r (the calling lane, when `hit`): it joins
-// the frontier of round r + 1 unless already there.  Wave-uniform call.
-__device__ __forceinline__ void join_next(const WArgs& a, int r, int v, bool hit, WQueue& q) {
-  const int np = (r + 1) & 1;
-  bool first = false;
-  int deg = 0;
-  if (hit) {
-    const u64 bit = 1ull << (v & 63);
-    u64* wd = &a.inq[np][v >> 6];
-    if (!(ld_relaxed(wd) & bit)) first = !(atom_or(wd, bit) & bit);
-    if (first) deg = a.rp[v + 1] - a.rp[v];
+  static __device__ __forceinline__ u64 entry(int v, int, int i) {
+    return (u64)(unsigned)v | ((u64)(unsigned)i << 32);
   }
-  const bool small = first && deg < kWBig;
-  const u64 mask = __ballot(small);
-  if (mask) {
-    if (small) q.buf[q.cnt + __popcll(mask & lanes_below())] = v;
-    q.cnt += __popcll(mask);
-    if (q.cnt > kWWaveBuf - kWave) wq_flush(a, r, q);
+  static __device__ __forceinline__ u64 row_entry(int v, int) {
+    return (u64)(unsigned)v | ((u64)kWhole << 32);
   }
-  const int nch = (first && deg >= kWBig) ? (deg + kWChunk - 1) / kWChunk : 0;
-  if (__ballot(nch > 0)) {
-    const int incl = wave_incl_scan(nch);
-    unsigned base = 0;
-    if (lane_id() == kWave - 1) base = atom_add(&a.ctrl->slot[(r + 1) % 3].cn, (unsigned)incl);
-    base = (unsigned)__shfl((int)base, kWave - 1, kWave) + (unsigned)(incl - nch);
-    for (int k = 0; k < nch; ++k) {
-      a.cu[np][base + k] = v;
-      a.ck[np][base + k] = k;
+  static __device__ __forceinline__ int words(const WArgs& a) { return a.nw; }
+  static __device__ __forceinline__ bool scans(const SessPlan<State>& p) { return p.scan != 0; }
+
+  // Relax up to E edges per lane.  near: targets that drop below hi join the
+  // next frontier; with `split`, edges of the other kind are left alone.
+  template <int E, class Sink>
+  static __device__ __forceinline__ void relax(const WArgs& a, bool near, bool lite, unsigned hi, u64* next,
+                                               const int* v, const unsigned* cand, const bool* has0,
+                                               Sink& sink, SessCount& c) {
+    unsigned cur[E];
+    bool go[E], has[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) has[i] = has0[i];
+    if (E > 1 && a.split) {
+      // (a stale word lacks bits, no more)
+      u64 f[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) f[i] = has[i] ? a.fin[v[i] >> 6] : 0ull;
+#pragma unroll
+      for (int i = 0; i < E; ++i) has[i] = has[i] && !((f[i] >> (v[i] & 63)) & 1ull);
     }
-  }
-}
-
-// Relax up to four edges per lane (has[i]: edge i exists; du[i] + wt[i] is
-// its candidate).  Wave-uniform call.
-__device__ __forceinline__ void relax4(const WArgs& a, int r, const int* v, const unsigned* cand,
-                                       const bool* has, WQueue& q) {
-  unsigned cur[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) cur[i] = has[i] ? (unsigned)a.dist[v[i]] : 0u;
-  bool hit[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    hit[i] = false;
-    if (has[i] && cand[i] < cur[i]) hit[i] = cand[i] < umin_atomic(&a.dist[v[i]], cand[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) join_next(a, r, v[i], hit[i], q);
-}
-
-// Sub-queue holding virtual entry i: largest s with pre[s] <= i.
-__device__ __forceinline__ int wstripe_of(const unsigned* pre, unsigned i) {
-  int lo = 0;
-#pragma unroll
-  for (int step = kStripes / 2; step > 0; step >>= 1)
-    if (pre[lo + step] <= i) lo += step;
-  return lo;
-}
-
-// One round: the frontier of slot r % 3 (sub-queues and chunks of parity r & 1).
-__global__ __launch_bounds__(kWBlock) void wsssp_round(WArgs a, int r, int max_rounds) {
-  __shared__ unsigned pre[kStripes + 1];
-  __shared__ int32_t qbuf[kWBlock / kWave][kWWaveBuf];
-  WCtrl* c = a.ctrl;
-  const WSlot* in = &c->slot[r % 3];
-  if (threadIdx.x == 0) {
-    unsigned acc = 0;
-    for (int t = 0; t < kStripes; ++t) {
-      pre[t] = acc;
-      acc += ld_relaxed(&in->s[t].qn);
+    for (int i = 0; i < E; ++i) {
+      // (the distance as it is now: an older, larger one would cost an atomic,
+      // and those on a hub's line run one after another)
+      cur[i] = 0;
+      if (has[i]) cur[i] = (unsigned)ld_relaxed(&a.dist[v[i]]);
     }
-    pre[kStripes] = acc;
-  }
-  __syncthreads();
-  const unsigned qn = pre[kStripes], cn = ld_relaxed(&in->cn);
-  if (ld_relaxed(&c->run.done)) return;
-  if (qn == 0 && cn == 0) {
-    // every workgroup reads the same counts: the run ends here
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      c->run.done = 1;
-      c->run.last_round = r;
-    }
-    return;
-  }
-  if (r >= max_rounds) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) c->run.done = 2;
-    return;
-  }
-  if (blockIdx.x == 0) {
-    // the slot two rounds ahead is next filled by round r + 1
-    WSlot* z = &c->slot[(r + 2) % 3];
-    if (threadIdx.x < kStripes) z->s[threadIdx.x].qn = 0;
-    if (threadIdx.x == kStripes) z->cn = 0;
-  }
-  const int p = r & 1;
-  const int lane = lane_id();
-  const unsigned gw = (blockIdx.x * kWBlock + threadIdx.x) / kWave;
-  const unsigned nwaves = gridDim.x * kWBlock / kWave;
-  WQueue q{qbuf[threadIdx.x / kWave], 0};
-
-  // big-degree rows: one chunk of kWChunk edges per wave, four per lane
-  for (unsigned ch = gw; ch < cn; ch += nwaves) {
-    const int u = a.cu[p][ch];
-    const int k = a.ck[p][ch];
-    const unsigned du = (unsigned)a.dist[u];
-    const int e0 = a.rp[u] + k * kWChunk;
-    const int e1 = min(e0 + kWChunk, a.rp[u + 1]);
-    if (k == 0 && lane == 0) atomicAnd(&a.inq[p][u >> 6], ~(1ull << (u & 63)));
-    int v[4];
-    unsigned cand[4];
-    bool has[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = e0 + i * kWave + lane;
-      has[i] = e < e1;
-      v[i] = has[i] ? a.col[e] : 0;
-      cand[i] = has[i] ? du + (unsigned)a.wt[e] : 0u;
-    }
-    relax4(a, r, v, cand, has, q);
-  }
-
-  // small-degree nodes: 64 per wave, the union of their rows
-  for (unsigned base = gw * kWave; base < qn; base += nwaves * kWave) {
-    const unsigned i = base + lane;
-    int rs = 0, deg = 0;
-    unsigned du = 0;
-    if (i < qn) {
-      const int t = wstripe_of(pre, i);
-      const int u = a.q[p][(size_t)t * (size_t)a.n + (i - pre[t])];
-      rs = a.rp[u];
-      deg = a.rp[u + 1] - rs;
-      du = (unsigned)a.dist[u];
-      atomicAnd(&a.inq[p][u >> 6], ~(1ull << (u & 63)));
-    }
-    const int incl = wave_incl_scan(deg);
-    const int total = __shfl(incl, kWave - 1, kWave);
-    for (int eb = 0; eb < total; eb += 4 * kWave) {
-      int v[4];
-      unsigned cand[4];
-      bool has[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int x = eb + t * kWave + lane;
-        has[t] = x < total;
-        const int j = wave_owner(incl, has[t] ? x : total - 1);
-        const int inc_j = __shfl(incl, j, kWave);
-        const int deg_j = __shfl(deg, j, kWave);
-        const int rs_j = __shfl(rs, j, kWave);
-        const unsigned du_j = (unsigned)__shfl((int)du, j, kWave);
-        const int e = rs_j + (x - (inc_j - deg_j));
-        v[t] = has[t] ? a.col[e] : 0;
-        cand[t] = has[t] ? du_j + (unsigned)a.wt[e] : 0u;
+    if constexpr (E == 1) {
+      // latency: the claim of the frontier bit travels with the minimum.  If
+      // another relaxation got there first, v has dropped in this round all the
+      // same and belongs in the next frontier.
+      go[0] = has[0] && cand[0] < cur[0];
+      bool first = false;
+      int deg = 0;
+      if (go[0]) {
+        const u64 bit = 1ull << (v[0] & 63);
+        umin_atomic(&a.dist[v[0]], cand[0]);
+        if (near && cand[0] < hi) {
+          first = !(atom_or(&next[v[0] >> 6], bit) & bit);
+          deg = near_degree(a, lite, v[0]);
+        }
       }
-      relax4(a, r, v, cand, has, q);
-    }
-  }
-  wq_flush(a, r, q);
-}
-
-// dist = -1 everywhere but the source; the frontier of round 0 is the source.
-__global__ __launch_bounds__(kWBlock) void wsssp_init(WArgs a, int source) {
-  const int tid = blockIdx.x * kWBlock + threadIdx.x;
-  const int nt = gridDim.x * kWBlock;
-  for (int i = tid; i < a.n; i += nt) a.dist[i] = i == source ? 0 : -1;
-  if (tid == 0) {
-    WCtrl* c = a.ctrl;
-    memset(&c->slot[1], 0, sizeof(WSlot));
-    memset(&c->slot[2], 0, sizeof(WSlot));
-    memset(&c->run, 0, sizeof(WRun));
-    const int deg = a.rp[source + 1] - a.rp[source];
-    memset(&c->slot[0], 0, sizeof(WSlot));
-    if (deg < kWBig) {
-      c->slot[0].s[0].qn = 1;
-      a.q[0][0] = source;
+      put(first, v[0], deg, sink, c);
     } else {
-      const int nch = (deg + kWChunk - 1) / kWChunk;
-      c->slot[0].cn = (unsigned)nch;
-      for (int k = 0; k < nch; ++k) {
-        a.cu[0][k] = source;
-        a.ck[0][k] = k;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        go[i] = false;
+        if (has[i] && cand[i] < cur[i]) go[i] = cand[i] < umin_atomic(&a.dist[v[i]], cand[i]);
+      }
+      if (!near) return;
+      bool first[E];
+      int deg[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        first[i] = false;
+        if (go[i] && cand[i] < hi) {
+          const u64 bit = 1ull << (v[i] & 63);
+          u64* w = &next[v[i] >> 6];
+          if (!(ld_relaxed(w) & bit)) first[i] = !(atom_or(w, bit) & bit);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < E; ++i) deg[i] = first[i] ? near_degree(a, lite, v[i]) : 0;
+#pragma unroll
+      for (int i = 0; i < E; ++i) put(first[i], v[i], deg[i], sink, c);
+    }
+  }
+
+  // Edges of v's row a near round looks at: in a bucket no wider than delta an
+  // edge of weight delta or more reaches past it.
+  static __device__ __forceinline__ int near_degree(const WArgs& a, bool lite, int v) {
+    return lite ? a.light[v] : a.rp[v + 1] - a.rp[v];
+  }
+  static __device__ __forceinline__ bool lite_rows(const WArgs& a, const State& u) {
+    return a.light && uniform(u.width) <= a.delta;
+  }
+
+  template <class Sink>
+  static __device__ __forceinline__ void put(bool first, int v, int deg, Sink& sink,
+                                             SessCount& c) {
+    const bool ok = first && deg > 0;
+    if (ok) c.mf += (unsigned)deg;
+    c.nf += (unsigned)__popcll(__ballot(ok));
+    sink.add(ok, v, deg);
+  }
+
+  template <int E, class Src, class Sink>
+  static __device__ __forceinline__ void push(const WArgs& a, int* own, const State& u,
+                                              unsigned ngroups, unsigned gw, unsigned nwaves,
+                                              const Src& src, Sink& sink, SessCount& c) {
+    const bool near = uniform(u.phase) == kNear;
+    const unsigned hi = uniform(u.hi);
+    const unsigned par = uniform(u.par);
+    u64* mine = par ? a.inq[1] : a.inq[0];
+    u64* next = par ? a.inq[0] : a.inq[1];
+    const bool split = a.split != 0;
+    const bool lite = lite_rows(a, u);
+    unsigned du = 0;
+    walk_rows<E>(
+        own, ngroups, gw, nwaves, src,
+        [&](u64 e, unsigned part, int& rs, int& deg) {
+          du = 0;
+          if (e == kNoEntry) return;
+          const int v = (int)(unsigned)e;
+          const unsigned piece = (unsigned)(e >> 32);
+          rs = a.rp[v];
+          deg = near_degree(a, near && lite, v);
+          du = (unsigned)ld_relaxed(&a.dist[v]);
+          if (near && part == 0 && (piece == 0 || piece == kWhole))
+            atomicAnd(&mine[v >> 6], ~(1ull << (v & 63)));
+          if (piece != kWhole) {
+            rs += (int)piece * kPiece;
+            deg = min(kPiece, deg - (int)piece * kPiece);
+          }
+        },
+        [&](const int* o, const int* at, const bool* has0) {
+          int v[E];
+          unsigned cand[E];
+          bool has[E];
+#pragma unroll
+          for (int q = 0; q < E; ++q) {
+            const unsigned d = (unsigned)__shfl((int)du, o[q], kWave);
+            cand[q] = has0[q] ? d + (unsigned)a.wt[at[q]] : 0u;
+          }
+#pragma unroll
+          for (int q = 0; q < E; ++q) {
+            has[q] = has0[q] && (!split || (cand[q] < hi) == near);
+            v[q] = has[q] ? a.col[at[q]] : 0;
+          }
+          relax<E>(a, near, lite, hi, next, v, cand, has, sink, c);
+        });
+  }
+
+  // One wave per 64 nodes: rows of the nodes in [lo, hi) to the queue, and the
+  // number of reached nodes past it.  settled: they are final.
+  template <class Sink>
+  static __device__ __forceinline__ void collect(const WArgs& a, bool settled, bool lite,
+                                                 unsigned lo, unsigned hi,
+                                                 unsigned gw, unsigned nwaves, Sink& sink,
+                                                 SessCount& c) {
+    const int lane = lane_id();
+    for (unsigned w = gw; w < (unsigned)a.nw; w += 4 * nwaves) {
+      unsigned d[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const long long v = (long long)(w + q * nwaves) * kWave + lane;
+        d[q] = v < a.n ? (unsigned)ld_relaxed(&a.dist[v]) : kUnreached;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int v = (int)((w + q * nwaves) * kWave) + lane;
+        const bool in = d[q] >= lo && d[q] < hi;
+        if (d[q] >= hi && d[q] != kUnreached) c.scan += 1;
+        const u64 bits = __ballot(in);
+        if (!bits) continue;
+        if (settled && lane == 0) {
+          u64* f = &a.fin[w + q * nwaves];
+          st_relaxed64(f, ld_relaxed(f) | bits);
+        }
+        const int deg = in ? near_degree(a, lite && !settled, v) : 0;
+        put(in, v, deg, sink, c);
       }
     }
   }
+
+  template <class Sink>
+  static __device__ __forceinline__ void step(const WArgs& a, const SessArgs& x, Shared& sh,
+                                              Sink& sink, SessCount& c) {
+    const int wv = threadIdx.x / kWave;
+    const unsigned K = uniform(sh.p.K);
+    const unsigned nwaves = K * kSW;
+    const unsigned gw = (unsigned)wv * K + sh.rank;
+    const State& u = sh.p.u;
+    if (uniform(sh.p.scan)) {
+      collect(a, uniform(u.phase) == kSettled, lite_rows(a, u), uniform(u.lo), uniform(u.hi), gw, nwaves, sink, c);
+      return;
+    }
+    const QueueSrc<WeightPolicy> src = queue_src(sh, x.q[sh.p.qp]);
+    const unsigned ngroups = uniform(sh.pre_g[kSessSegs]);
+    if (uniform(sh.p.fe) <= nwaves * 2 * kWave)
+      push<1>(a, sh.own[wv], u, ngroups, gw, nwaves, src, sink, c);
+    else
+      push<4>(a, sh.own[wv], u, ngroups, gw, nwaves, src, sink, c);
+  }
+
+  template <class Sink>
+  static __device__ __forceinline__ void solo(const WArgs& a, Shared& sh, const u64* cur,
+                                              unsigned ncur, Sink& sink, SessCount& c) {
+    const int wv = threadIdx.x / kWave;
+    push<1>(a, sh.own[wv], sh.p.u, (ncur + kWave - 1) / kWave, (unsigned)wv, (unsigned)kSW,
+            ListSrc{cur, ncur}, sink, c);
+  }
+
+  // What follows the level just run, from the rows it put in the queue (nf, of
+  // mf edges) and, after a collection, the reached nodes past it.
+  static __device__ __forceinline__ void advance(const WArgs& a, Shared& sh, unsigned nf, u64 mf,
+                                                 u64 beyond, bool record) {
+    State u = sh.p.u;
+    unsigned done = 0;
+    u.steps += 1;
+    switch (u.phase) {
+      case kNear:
+        u.rounds += 1;
+        u.par ^= 1;
+        if (nf) break;
+        if (a.split)
+          u.phase = kSettled;
+        else
+          next_bucket(u, a.delta);
+        break;
+      case kSettled:
+        // (nobody with an edge: what lies past the bucket is as it was)
+        if (nf)
+          u.phase = kHeavy;
+        else if (u.beyond)
+          next_bucket(u, min(u.width * 2, 1u << 30));
+        else
+          done = 1;
+        break;
+      case kHeavy:
+        // past the bulk of the edges, buckets of little work: fewer, wider ones
+        u.settled += sh.p.fe;
+        next_bucket(u, sh.p.fe < kSmallBucket && u.settled > a.half ? min(u.width * 2, 1u << 30)
+                                                                    : a.delta);
+        break;
+      default:
+        u.beyond = (unsigned)beyond;
+        if (nf)
+          u.phase = kNear;
+        else if (a.split)
+          u.phase = kSettled;
+        else if (beyond)
+          next_bucket(u, min(u.width * 2, 1u << 30));
+        else
+          done = 1;
+    }
+    if (u.steps > a.max_rounds) done = 2;
+    set_plan<WeightPolicy>(sh, done != 0, u.phase == kSettled || u.phase == kCollect, mf, a.nw,
+                           kSoloCap);
+    if (lane_id() == 0) {
+      sh.p.u = u;
+      if (done && record) {
+        a.ctrl->done = done;
+        a.ctrl->rounds = u.rounds;
+      }
+    }
+  }
+  static __device__ __forceinline__ void next_bucket(State& u, unsigned width) {
+    u.phase = kCollect;
+    u.lo = u.hi;
+    u.width = width;
+    u.hi = min(u.lo + width, 0x7fffffffu);
+  }
+
+  static __device__ __forceinline__ void begin(const WArgs& a, const SessArgs& x, Shared& sh) {
+    const int s = x.source;
+    const int deg = near_degree(a, a.light != nullptr, s);
+    if (lane_id() == 0) {
+      State& u = sh.p.u;
+      u.phase = kCollect;       // as if a collection had found the source
+      u.par = 0;
+      u.lo = 0;
+      u.hi = u.width = a.delta;
+      u.rounds = u.steps = u.beyond = u.settled = 0;
+      sh.stage[0] = row_entry(s, deg);
+      st_relaxed64(&x.q[0][0], row_entry(s, deg));
+    }
+    wave_sync();
+    advance(a, sh, deg > 0 ? 1u : 0u, (u64)deg, 0ull, true);
+  }
+};
+
+__global__ __launch_bounds__(kSB, 4) void wsssp_session(WArgs a, SessArgs x) {
+  __shared__ SessShared<WeightPolicy> sh;
+  session<WeightPolicy>(a, x, sh);
 }
 
-// After the run: reached nodes and the sum of their out-degrees (E_reach,
-// the GTEPS numerator).
-__global__ __launch_bounds__(kWBlock) void wsssp_close(WArgs a) {
+// dist = -1 everywhere but the source, control block clear.
+__global__ __launch_bounds__(kSB) void wsssp_init(WArgs a, int source) {
+  const unsigned tid = blockIdx.x * kSB + threadIdx.x, nt = gridDim.x * kSB;
+  if (tid == 0) a.hm->t_start = wall_clock64();
+  u64* c = reinterpret_cast<u64*>(a.ctrl);
+  for (unsigned i = tid; i < sizeof(WCtrl) / 8; i += nt) c[i] = 0;
+  if (a.split)
+    for (unsigned i = tid; i < (unsigned)a.nw; i += nt) a.fin[i] = 0;
+  for (unsigned i = tid; i < (unsigned)a.n; i += nt) a.dist[i] = (int)i == source ? 0 : -1;
+}
+
+// A copy of the rows with the edges lighter than delta first (one wave a row).
+__global__ __launch_bounds__(kSB) void split_rows(int32_t n, const int32_t* rp, const int32_t* col,
+                                                  const int32_t* wt, int32_t delta, int32_t* scol,
+                                                  int32_t* swt, int32_t* light) {
+  const int lane = lane_id();
+  const int nwaves = (int)gridDim.x * kSW;
+  for (int v = (int)blockIdx.x * kSW + (int)threadIdx.x / kWave; v < n; v += nwaves) {
+    const int s = rp[v], e = rp[v + 1];
+    int cnt = 0;
+    for (int i = s; i < e; i += kWave)
+      cnt += __popcll(__ballot(i + lane < e && wt[i + lane] < delta));
+    int nl = s, nh = s + cnt;
+    for (int i = s; i < e; i += kWave) {
+      const bool in = i + lane < e;
+      const int w = in ? wt[i + lane] : 0;
+      const u64 lm = __ballot(in && w < delta), hm = __ballot(in && w >= delta);
+      if (in) {
+        const int at = w < delta ? nl + __popcll(lm & lanes_below()) : nh + __popcll(hm & lanes_below());
+        scol[at] = col[i + lane];
+        swt[at] = w;
+      }
+      nl += __popcll(lm);
+      nh += __popcll(hm);
+    }
+    if (lane == 0) light[v] = cnt;
+  }
+}
+
+// After the run: reached nodes and the sum of their out-degrees (E_reach, the
+// GTEPS numerator); the last workgroup reports the end to the host.
+__global__ __launch_bounds__(kSB) void wsssp_close(WArgs a) {
   u64 reached = 0, se = 0;
-  const int tid = blockIdx.x * kWBlock + threadIdx.x;
-  const int nt = gridDim.x * kWBlock;
+  const int tid = blockIdx.x * kSB + threadIdx.x;
+  const int nt = gridDim.x * kSB;
   for (int i = tid; i < a.n; i += nt)
     if (a.dist[i] >= 0) {
       reached += 1;
       se += (u64)(a.rp[i + 1] - a.rp[i]);
     }
-  __shared__ u64 red[2][kWBlock / kWave];
+  __shared__ u64 red[2][kSW];
   reached = wave_sum(reached);
   se = wave_sum(se);
   if (lane_id() == 0) {
@@ -313,10 +478,33 @@ __global__ __launch_bounds__(kWBlock) void wsssp_close(WArgs a) {
     red[1][threadIdx.x / kWave] = se;
   }
   __syncthreads();
-  if (threadIdx.x < 2) {
-    u64 x = 0;
-    for (int i = 0; i < kWBlock / kWave; ++i) x += red[threadIdx.x][i];
-    if (x) atom_add(&a.ctrl->run.part[blockIdx.x % kStripes][threadIdx.x], x);
+  if (threadIdx.x >= kWave) return;
+  int last = 0;
+  if (threadIdx.x == 0) {
+    u64 r = 0, e = 0;
+    for (int i = 0; i < kSW; ++i) {
+      r += red[0][i];
+      e += red[1][i];
+    }
+    WCtrl::Part& p = a.ctrl->part[blockIdx.x % kStripes];
+    if (r) {
+      atom_add(&p.reached, r);
+      atom_add(&p.edges, e);
+    }
+    wait_all();
+    last = atom_add(&a.ctrl->closed, 1u) == gridDim.x - 1;
+  }
+  if (!__builtin_amdgcn_readfirstlane(last)) return;
+  const bool st = lane_id() < kStripes;
+  const u64 r = wave_sum(st ? ld_relaxed(&a.ctrl->part[lane_id()].reached) : 0ull);
+  const u64 e = wave_sum(st ? ld_relaxed(&a.ctrl->part[lane_id()].edges) : 0ull);
+  if (threadIdx.x == 0) {
+    a.hm->rounds = a.ctrl->rounds;
+    a.hm->done = a.ctrl->done ? a.ctrl->done : 2u;   // 0: a wait timed out
+    a.hm->reached = r;
+    a.hm->source_edges = e;
+    a.hm->t_end = wall_clock64();
+    __hip_atomic_store(&a.hm->end_tag, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -326,28 +514,28 @@ namespace {
 struct WWs {
   Ctx* ctx = nullptr;
   hipStream_t stream = nullptr;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  int32_t* q[2] = {nullptr, nullptr};
-  int32_t* cu[2] = {nullptr, nullptr};
-  int32_t* ck[2] = {nullptr, nullptr};
+  hipEvent_t ev1 = nullptr;
+  u64* q[2] = {nullptr, nullptr};
   u64* inq[2] = {nullptr, nullptr};
+  u64* fin = nullptr;
   int32_t* dist = nullptr;
   WCtrl* ctrl = nullptr;
-  WCtrl* h_ctrl = nullptr;
+  WMirror* h_m = nullptr;
+  WMirror* d_m = nullptr;
+  unsigned seq = 0;
   size_t bytes = 0;
 
   ~WWs() {
+    if (stream) hipStreamSynchronize(stream);
     for (int i = 0; i < 2; ++i) {
       dev_free(ctx, q[i], 0);
-      dev_free(ctx, cu[i], 0);
-      dev_free(ctx, ck[i], 0);
       dev_free(ctx, inq[i], 0);
     }
+    dev_free(ctx, fin, 0);
     dev_free(ctx, dist, 0);
     dev_free(ctx, ctrl, 0);
     if (ctx) ctx->used -= bytes;
-    if (h_ctrl) hipHostFree(h_ctrl);
-    if (ev0) hipEventDestroy(ev0);
+    if (h_m) hipHostFree(h_m);
     if (ev1) hipEventDestroy(ev1);
     if (stream) hipStreamDestroy(stream);
   }
@@ -357,8 +545,6 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
   std::unique_ptr<WWs> w(new WWs());
   w->ctx = ctx;
   const size_t n = (size_t)g->n, nw = (n + 63) / 64;
-  // chunks per round: every big node at most once, ceil(deg / kWChunk) each
-  const size_t chunk_cap = (size_t)(g->m / kWChunk) + (size_t)(g->m / kWBig) + 64;
   WWs* wp = w.get();
   auto alloc = [&](void** p, size_t bytes) -> dawn_status {
     dawn_status s = dev_alloc(ctx, p, bytes);
@@ -366,28 +552,37 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
     return s;
   };
   for (int i = 0; i < 2; ++i) {
-    DAWN_TRY(alloc((void**)&w->q[i], (size_t)kStripes * n * 4));
-    DAWN_TRY(alloc((void**)&w->cu[i], chunk_cap * 4));
-    DAWN_TRY(alloc((void**)&w->ck[i], chunk_cap * 4));
+    DAWN_TRY(alloc((void**)&w->q[i], (size_t)kSessStripes * sess_queue_cap(g->n, g->m, kWeightPiece) * 8));
     DAWN_TRY(alloc((void**)&w->inq[i], nw * 8 + 64));
     DAWN_HIP(hipMemset(w->inq[i], 0, nw * 8 + 64));
   }
+  DAWN_TRY(alloc((void**)&w->fin, nw * 8));
   DAWN_TRY(alloc((void**)&w->dist, n * 4));
   DAWN_TRY(alloc((void**)&w->ctrl, sizeof(WCtrl)));
-  DAWN_HIP(hipMemset(w->ctrl, 0, sizeof(WCtrl)));
-  DAWN_HIP(hipHostMalloc((void**)&w->h_ctrl, sizeof(WCtrl), hipHostMallocDefault));
+  DAWN_HIP(hipHostMalloc((void**)&w->h_m, sizeof(WMirror),
+                         hipHostMallocCoherent | hipHostMallocMapped));
+  memset(w->h_m, 0, sizeof(WMirror));
+  DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
   DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
-  DAWN_HIP(hipEventCreate(&w->ev0));
-  DAWN_HIP(hipEventCreate(&w->ev1));
+  DAWN_HIP(hipEventCreateWithFlags(&w->ev1, hipEventDisableTiming));
   *out = std::move(w);
   return DAWN_OK;
 }
 
-}  // namespace
+// Spin until run `seq` reports its end, or the work queued before ev1 has all
+// run (with or without the report).
+hipError_t wait_report(WWs* w, unsigned seq) {
+  for (unsigned spin = 1;; ++spin) {
+    if (__atomic_load_n(&w->h_m->end_tag, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+    if ((spin & 63) == 0) {
+      const hipError_t e = hipEventQuery(w->ev1);
+      if (e != hipErrorNotReady) return e;
+    }
+    __builtin_ia32_pause();
+  }
+}
 
-// Rounds queued per host check of the run state: the first batch covers the
-// graph's last run, later ones double.
-constexpr int kWRoundsFirst = 16;
+}  // namespace
 
 struct WsspPool {
   std::vector<std::unique_ptr<WWs>> ws;
@@ -396,6 +591,48 @@ struct WsspPool {
 void wsssp_pool_free(GraphRec* g) {
   delete reinterpret_cast<WsspPool*>(g->wpool);
   g->wpool = nullptr;
+}
+
+void wsssp_weights_free(GraphRec* g) {
+  Ctx* ctx = g->ctx;
+  const size_t mb = (size_t)std::max(g->m, 1LL) * 4;
+  if (g->wt) dev_free(ctx, g->wt, mb);
+  if (g->w_light) {
+    dev_free(ctx, g->w_col, mb);
+    dev_free(ctx, g->w_wt, mb);
+    dev_free(ctx, g->w_light, (size_t)g->n * 4);
+  }
+  g->wt = g->w_col = g->w_wt = g->w_light = nullptr;
+}
+
+dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, int32_t* wt, int32_t max_w, double mean_w,
+                         WeightRows* out) {
+  const double mean_deg = std::max((double)g->m / (double)g->n, 1.0);
+  double delta = kDelta * mean_w / mean_deg;
+  if (delta >= (double)max_w) delta = kDeltaWhole * mean_w / mean_deg;
+  out->delta = (int32_t)std::min(std::max(delta, 1.0), 1e9);
+  out->col = out->wt = out->light = nullptr;
+  if (out->delta >= max_w || g->m == 0) return DAWN_OK;
+  const size_t mb = (size_t)g->m * 4, nb = (size_t)g->n * 4;
+  // only out of plenty: the copy must not take the room of what has none other
+  const uint64_t used = ctx->used.load() + ctx->reserved.load();
+  if (used > ctx->budget || 2 * mb + nb > (ctx->budget - used) / 8) return DAWN_OK;
+  if (dev_alloc(ctx, (void**)&out->col, mb) != DAWN_OK ||
+      dev_alloc(ctx, (void**)&out->wt, mb) != DAWN_OK ||
+      dev_alloc(ctx, (void**)&out->light, nb) != DAWN_OK) {
+    // no room for the copy: near rounds then look at whole rows
+    clear_error();
+    if (out->col) dev_free(ctx, out->col, mb);
+    if (out->wt) dev_free(ctx, out->wt, mb);
+    out->col = out->wt = out->light = nullptr;
+    return DAWN_OK;
+  }
+  hipLaunchKernelGGL(split_rows, dim3(ctx->num_cu * 4), dim3(kSB), 0, 0, g->n, g->rp, g->col, wt,
+                     out->delta, out->col, out->wt, out->light);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e != hipSuccess) return fail(DAWN_E_DEVICE, "weights layout: %s", hipGetErrorString(e));
+  return DAWN_OK;
 }
 
 dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool device_out,
@@ -418,80 +655,76 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
   a.nw = (g->n + 63) / 64;
   a.rp = g->rp;
   a.col = g->col;
-  a.wt = g->wt;
   a.dist = device_out ? dist : w->dist;
-  for (int i = 0; i < 2; ++i) {
-    a.q[i] = w->q[i];
-    a.cu[i] = w->cu[i];
-    a.ck[i] = w->ck[i];
-    a.inq[i] = w->inq[i];
-  }
+  a.inq[0] = w->inq[0];
+  a.inq[1] = w->inq[1];
   a.ctrl = w->ctrl;
-  hipStream_t s = w->stream;
-  const int fill = std::max(1, std::min((g->n + kWBlock - 1) / kWBlock, ctx->num_cu * 8));
-  const int grid = ctx->num_cu * 8;
-  const int max_rounds = g->n + 1;
-  dawn_status st = DAWN_OK;
-  hipError_t e = hipEventRecord(w->ev0, s);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(wsssp_init, dim3(fill), dim3(kWBlock), 0, s, a, source);
-    e = hipGetLastError();
-  }
-  int launches = 1, queued = 0;
-  int batch = std::max(g->wsssp_hint.load(std::memory_order_relaxed) + 1, kWRoundsFirst);
-  while (e == hipSuccess) {
-    for (int i = 0; i < batch; ++i)
-      hipLaunchKernelGGL(wsssp_round, dim3(grid), dim3(kWBlock), 0, s, a, queued + i, max_rounds);
-    e = hipGetLastError();
-    launches += batch;
-    queued += batch;
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(&w->h_ctrl->run, &w->ctrl->run, sizeof(WRun), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess || w->h_ctrl->run.done) break;
-    if (queued > max_rounds + 1) {
-      st = fail(DAWN_E_DEVICE, "weighted level loop did not terminate");
-      break;
+  a.hm = w->d_m;
+  w->seq = w->seq % 0x7fffffffu + 1;
+  a.seq = w->seq;
+  a.fin = w->fin;
+  a.half = (unsigned)(g->m / 2);
+  {
+    std::lock_guard<std::mutex> lk(g->mu);
+    a.wt = g->wt;
+    a.delta = (unsigned)g->w_delta;
+    a.split = g->w_delta < g->max_w ? 1 : 0;
+    if (a.split && g->w_light) {
+      a.col = g->w_col;
+      a.wt = g->w_wt;
+      a.light = g->w_light;
     }
-    batch = std::min(batch * 2, 1024);
   }
-  if (e == hipSuccess && st == DAWN_OK) {
-    if (w->h_ctrl->run.done == 2) st = fail(DAWN_E_DEVICE, "watchdog: more than n + 1 rounds");
+  // a near round but a bucket's last settles a node, and a bucket takes at most
+  // four levels more
+  a.max_rounds = (unsigned)std::min<long long>(6ll * g->n + 256, 0xffffffffll);
+  SessArgs x;
+  x.sc = &w->ctrl->sess;
+  x.q[0] = w->q[0];
+  x.q[1] = w->q[1];
+  x.qcap = (unsigned)sess_queue_cap(g->n, g->m, kWeightPiece);
+  x.ccap = (unsigned)sess_cluster_cap(x.qcap);
+  x.source = source;
+  hipStream_t s = w->stream;
+  const int fill = std::max(1, std::min((g->n + kSB - 1) / kSB, ctx->num_cu * 4));
+  static std::atomic<int> occ_cache{0};
+  int occ = occ_cache.load(std::memory_order_relaxed);
+  hipError_t e = hipSuccess;
+  if (!occ) {
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, wsssp_session, kSB, 0);
+    occ = std::max(occ, 1);
+    if (e == hipSuccess) occ_cache.store(occ, std::memory_order_relaxed);
   }
-  if (e == hipSuccess && st == DAWN_OK) {
-    hipLaunchKernelGGL(wsssp_close, dim3(fill), dim3(kWBlock), 0, s, a);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(wsssp_init, dim3(fill), dim3(kSB), 0, s, a, source);
+    hipLaunchKernelGGL(wsssp_session, dim3(sess_grid(ctx, std::min(occ, kSessPerCu), a.nw, g->m)),
+                       dim3(kSB), 0, s, a, x);
+    hipLaunchKernelGGL(wsssp_close, dim3(fill), dim3(kSB), 0, s, a);
     e = hipGetLastError();
-    ++launches;
-    if (e == hipSuccess) e = hipEventRecord(w->ev1, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(w->h_ctrl, w->ctrl, sizeof(WCtrl), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess && !device_out)
-      e = hipMemcpyAsync(dist, w->dist, (size_t)g->n * 4, hipMemcpyDeviceToHost, s);
+  }
+  if (e == hipSuccess) e = hipEventRecord(w->ev1, s);
+  if (e == hipSuccess) e = wait_report(w.get(), a.seq);
+  dawn_status st = DAWN_OK;
+  if (e != hipSuccess)
+    st = fail(DAWN_E_DEVICE, "weighted SSSP: %s", hipGetErrorString(e));
+  else if (w->h_m->end_tag != a.seq || w->h_m->done != 1)
+    st = fail(DAWN_E_DEVICE, "weighted level loop did not finish");
+  if (st == DAWN_OK && !device_out) {
+    e = hipMemcpyAsync(dist, w->dist, (size_t)g->n * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) st = fail(DAWN_E_DEVICE, "weighted SSSP: %s", hipGetErrorString(e));
   }
-  if (e != hipSuccess) st = fail(DAWN_E_DEVICE, "weighted SSSP: %s", hipGetErrorString(e));
-  if (st != DAWN_OK) {
-    hipStreamSynchronize(s);
-    return st;   // the workspace is dropped (its bitmaps may hold bits)
-  }
-  const WRun& run = w->h_ctrl->run;
-  u64 reached = 0, source_edges = 0;
-  for (int i = 0; i < kStripes; ++i) {
-    reached += run.part[i][0];
-    source_edges += run.part[i][1];
-  }
-  g->wsssp_hint.store(run.last_round + 1, std::memory_order_relaxed);
+  if (st != DAWN_OK) return st;   // the workspace is dropped (its bitmaps may hold bits)
+  const WMirror& m = *w->h_m;
   if (stats) {
-    float ms = 0.f;
-    hipEventElapsedTime(&ms, w->ev0, w->ev1);
-    stats->levels = run.last_round;            // rounds that had a frontier
-    stats->push_levels = run.last_round;
+    stats->levels = std::max((int32_t)m.rounds, 1);   // rounds that had a frontier
+    stats->push_levels = stats->levels;
     stats->pull_levels = 0;
-    stats->launches = launches;
+    stats->launches = 3;
     stats->edges_examined = 0;                 // not counted by the weighted rounds
-    stats->source_edges = (int64_t)source_edges;
-    stats->reached = (int64_t)reached;
-    stats->kernel_ms = ms;
+    stats->source_edges = (int64_t)m.source_edges;
+    stats->reached = (int64_t)m.reached;
+    stats->kernel_ms = ctx->wall_khz > 0 ? (double)(m.t_end - m.t_start) / ctx->wall_khz : 0.0;
     stats->total_ms = (now_ns() - t0) / 1e6;
     stats->kernel_clock_ms = 0.0;
   }
