@@ -270,7 +270,9 @@ dawn_status dawn_sssp_noalloc(dawn_ctx *ctx, int32_t graph, int32_t source, int3
  * 64-bit words per node, and one level step advances all of them (the level
  * step of Algorithms 1/2 applied per bit).  Each level's direction and the
  * end of the run are decided on the device; the host checks a batch once per
- * chunk of queued levels.  k == 0 is a no-op.
+ * chunk of queued levels.  A narrow batch (at most 512 sources) runs all its
+ * levels in one launch instead, unless the graph is very large or
+ * `direction` forces pushes.  k == 0 is a no-op.
  * Errors: INVALID_ARG, NOT_FOUND, NO_MEMORY, DEVICE. */
 dawn_status dawn_mssp(dawn_ctx *ctx, int32_t graph, const int32_t *sources, int32_t k,
                       int32_t *dist, uint32_t flags, dawn_run_stats *stats);
@@ -288,7 +290,8 @@ dawn_status dawn_mssp(dawn_ctx *ctx, int32_t graph, const int32_t *sources, int3
  * earlier batches of 4096 sources may be written, later ones are not).
  * Levels are queued as separate launches up to the depth of the graph's last
  * finished run, then one cooperative kernel runs any further levels with a
- * grid barrier between steps; the level bit-planes are allocated for the
+ * grid barrier between steps; a narrow batch (see dawn_mssp) has all its levels
+ * in one launch.  The level bit-planes are allocated for the
  * deepest possible run (min(16, bit_length(n)) planes of n x 64-lane words
  * per batch word, i.e. at most half the size of a full batch's rows).
  * Buffers stay owned by the caller and must stay valid until the stream has

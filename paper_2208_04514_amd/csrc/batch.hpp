@@ -42,7 +42,25 @@ struct alignas(kLine) BatchRun {
   int pull;                     // 1: the level being expanded pulls
   int last_nonempty;            // last level that found new bits
   int push_levels, pull_levels;
+  int vis_buf;                  // 1: the visited rows are in nxt[0] (one-launch runs)
   u64 edges, reached, source_edges;
+};
+
+// Control block of a one-launch run (bsession.hip): the levels' record and
+// barrier, the sources that found something per level (three levels in turn)
+// and the run's totals, each over stripes.
+struct alignas(kLine) FusedLanes {
+  u64 w[8];
+};
+struct alignas(kLine) FusedPart {
+  u64 edges, reached, degs;
+};
+struct FusedCtrl {
+  SessCtrl sess;
+  FusedLanes lact[3][kStripes];
+  FusedPart part[kStripes];
+  alignas(kLine) unsigned level;    // next level to run
+  unsigned touched;                 // nodes with a nonzero row
 };
 
 struct BatchCtrl {
@@ -99,11 +117,15 @@ struct BatchArgs {
   int32_t big_b;                // push: out-degree from which a node's edges go by chunks
   int32_t wide_scan;            // narrow rows: in-list length scanned by the whole wave
   int32_t sparse_words;         // push one edge per lane for nodes with <= this many words
+  int32_t fused;                // a one-launch run's rows: the emission takes the buffer
+                                //   ctrl->run.vis_buf names
   unsigned* flags;              // [0] the workspace may hold bits (set by the seed, cleared by
                                 //   a complete emission), [1] run status: 0 ok, 1 invalid
                                 //   source, 2 watchdog (device-ordered calls report it)
 };
 
+// flags[kFlagDirty]: bit 0 any array may hold bits, bit 1 the frontier bitmaps
+// may (what a finished one-launch run leaves)
 constexpr int kFlagDirty = 0;
 constexpr int kFlagStatus = 1;
 
@@ -134,6 +156,8 @@ struct BatchWs {
   int32_t* src = nullptr;
   int32_t* lane = nullptr;      // lane of each seeded source
   unsigned* flags = nullptr;    // see BatchArgs::flags
+  FusedCtrl* fused = nullptr;   // behind flags in the same allocation
+  FusedPart* h_part = nullptr;  // pinned read-back of its totals
   BatchCtrl* h_ctrl = nullptr;
   // the last work enqueued on the workspace (by a call on any stream); whoever
   // takes it next makes its stream wait for this event first
@@ -165,7 +189,7 @@ dawn_status batch_launch_emit(Ctx* ctx, const BatchArgs& a, int nplanes_used, co
                               int mode, hipStream_t s);
 dawn_status batch_launch_zero(Ctx* ctx, u64* p, size_t count, hipStream_t s);
 // Clear up to kZeroMax arrays in one launch.
-constexpr int kZeroMax = 26;
+constexpr int kZeroMax = 30;
 struct ZeroList {
   u64* p[kZeroMax];
   size_t count[kZeroMax];
@@ -185,6 +209,11 @@ dawn_status batch_launch_control(const BatchArgs& a, u64* act, int L, const dawn
                                  hipStream_t s);
 dawn_status batch_launch_seed(Ctx* ctx, const BatchArgs& a, const int32_t* d_src,
                               const int32_t* d_lane, int k, int L, bool live, hipStream_t s);
+// One-launch runs (bsession.hip): whether k sources take one.
+bool batch_session_fits(const GraphRec* g, const dawn_params& p, int k);
+dawn_status batch_session_seed_launch(const BatchArgs& a, FusedCtrl* fc, const int32_t* d_src,
+                                      int k, hipStream_t s);
+dawn_status batch_session_launch(Ctx* ctx, const BatchArgs& a, FusedCtrl* fc, hipStream_t s);
 bool batch_choose_pull(const dawn_params& p, const BatchLevelSum& last, int n, int W);
 
 }  // namespace dawn

@@ -964,7 +964,12 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
     D = min(bit_length_dev(ld_relaxed(&r.last_nonempty)), a.nplanes);
     if (D < emit_dmin<DMAX>() || D > DMAX) return;
   }
-  if ((mode & kEmitMarkClean) && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagDirty] = 0;
+  // a one-launch run ends in either of its row buffers; both are cleared
+  const bool swapped = a.fused && ld_relaxed(&a.ctrl->run.vis_buf);
+  u64* const visp = swapped ? a.nxt[0] : a.vis;
+  u64* const other = a.fused && (mode & kEmitMarkClean) ? (swapped ? a.vis : a.nxt[0]) : nullptr;
+  if ((mode & kEmitMarkClean) && blockIdx.x == 0 && threadIdx.x == 0)
+    a.flags[kFlagDirty] = a.fused ? 2u : 0u;
   // the row pointers of all lanes, staged once: a per-word global load in the
   // store loop would wait for every store before it
   __shared__ u64 srow[kMaxBatchLanes];
@@ -1016,7 +1021,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
       // words of one array in consecutive 16-byte loads, so the requests for
       // a line follow each other closely enough that it is fetched once
       // (lanes past the last node read node 0's row and drop it)
-      const ulonglong2* pv = reinterpret_cast<const ulonglong2*>(a.vis + base);
+      const ulonglong2* pv = reinterpret_cast<const ulonglong2*>(visp + base);
 #pragma unroll
       for (int q = 0; q < EG / 2; ++q) {
         x[2 * q] = x[2 * q + 1] = 0;
@@ -1041,11 +1046,16 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
       if (whole_clear && live) {
         // every lane is emitted: the words just read are cleared with the
         // same 16-byte accesses (the line is still in the cache)
-        ulonglong2* wv = reinterpret_cast<ulonglong2*>(a.vis + base);
+        ulonglong2* wv = reinterpret_cast<ulonglong2*>(visp + base);
         const ulonglong2 z = {0ull, 0ull};
 #pragma unroll
         for (int q = 0; q < EG / 2; ++q)
           if ((wm >> (2 * q)) & 3u) wv[q] = z;
+        if (other) {
+          ulonglong2* wo = reinterpret_cast<ulonglong2*>(other + base);
+#pragma unroll
+          for (int q = 0; q < EG / 2; ++q) wo[q] = z;
+        }
 #pragma unroll
         for (int d = 0; d < DMAX; ++d)
           if (d < D) {
@@ -1058,7 +1068,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < EG; ++e) x[e] = live && ((wm >> e) & 1u) ? a.vis[base + e] : 0;
+      for (int e = 0; e < EG; ++e) x[e] = live && ((wm >> e) & 1u) ? visp[base + e] : 0;
 #pragma unroll
       for (int d = 0; d < DMAX; ++d)
         if (d < D) {
@@ -1086,7 +1096,8 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
         }
       if (clear && live && !cleared) {
         const u64 rem = xe & ~em;
-        a.vis[base + e] = rem;
+        visp[base + e] = rem;
+        if (other) other[base + e] = 0;
 #pragma unroll
         for (int d = 0; d < DMAX; ++d)
           if (d < D) a.planes[d][base + e] = pe[d] & ~em;
@@ -1278,19 +1289,20 @@ __global__ void batch_seed(BatchArgs a, const int32_t* src, const int32_t* lane,
   }
 }
 
-// Start of a batched run: the control block is cleared, and the bitmap
-// arrays too when the workspace may still hold bits (its first run, or a run
-// that stopped before its emission); after a complete run the emission has
-// already left them clear.  z.p[0] is the control block.  clear_status:
-// reset the run status (device-ordered calls set it once per call instead).
-__global__ __launch_bounds__(kBatchBlock) void batch_prepare(ZeroList z, unsigned* flags,
-                                                            int clear_status) {
+// Start of a batched run: the first `always` arrays of the list are cleared (the
+// control block first of them); the next, up to `second`, when a one-launch
+// run has used them; every array when the workspace may still hold bits (its
+// first run, or a run that stopped before its emission).  After a complete run
+// the emission has left them clear.  clear_status: reset the run status
+// (device-ordered calls set it once per call instead).
+__global__ __launch_bounds__(kBatchBlock) void batch_prepare(ZeroList z, int always, int second,
+                                                            unsigned* flags, int clear_status) {
   // nothing in this launch writes the flag, so every workgroup reads the same
-  const bool dirty = ld_relaxed(&flags[kFlagDirty]) != 0;
+  const unsigned dirty = ld_relaxed(&flags[kFlagDirty]);
   const size_t t0 = blockIdx.x * (size_t)kBatchBlock + threadIdx.x;
   const size_t nt = (size_t)gridDim.x * kBatchBlock;
   for (int y = 0; y < z.k; ++y) {
-    if (y > 0 && !dirty) break;
+    if (y >= always && !(dirty & 1u) && !(y < second && (dirty & 2u))) break;
     u64* p = z.p[y];
     for (size_t i = t0; i < z.count[y]; i += nt) p[i] = 0;
   }
@@ -1377,6 +1389,7 @@ void batch_ws_destroy(BatchWs* w) {
   if (ctx) ctx->used -= w->bytes;
   if (ctx && w->plane_reserve) dev_unreserve(ctx, w->plane_reserve);
   if (w->h_ctrl) hipHostFree(w->h_ctrl);
+  if (w->h_part) hipHostFree(w->h_part);
   if (w->ev0) hipEventDestroy(w->ev0);
   if (w->ev1) hipEventDestroy(w->ev1);
   if (w->busy) hipEventDestroy(w->busy);
@@ -1421,12 +1434,16 @@ dawn_status batch_ws_create(Ctx* ctx, const GraphRec* g, int lanes, BatchWs** ou
   alloc((void**)&w->base, (size_t)kMaxBatchLanes * 4);
   alloc((void**)&w->src, (size_t)kMaxBatchLanes * 4);
   alloc((void**)&w->lane, (size_t)kMaxBatchLanes * 4);
-  alloc((void**)&w->flags, 256);
+  alloc((void**)&w->flags, 256 + sizeof(FusedCtrl));
+  w->fused = w->flags ? reinterpret_cast<FusedCtrl*>(reinterpret_cast<char*>(w->flags) + 256)
+                      : nullptr;
   if (s != DAWN_OK) {
     batch_ws_destroy(w);
     return s;
   }
   hipError_t e = hipHostMalloc((void**)&w->h_ctrl, sizeof(BatchCtrl), hipHostMallocDefault);
+  if (e == hipSuccess)
+    e = hipHostMalloc((void**)&w->h_part, kStripes * sizeof(FusedPart), hipHostMallocDefault);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking);
   w->own_stream = true;
   if (e == hipSuccess) e = hipEventCreate(&w->ev0);
@@ -1607,10 +1624,12 @@ dawn_status batch_launch_emit(Ctx* ctx, const BatchArgs& a, int nplanes_used, co
   if (mode & kEmitFromRun) {
     // the plane count is known on the device only: every variant is queued
     // and the one whose range holds it runs
+    // (of those the planes there are allow)
     DAWN_TRY((launch_emit_t<3, 16>(ctx, a, 0, d_emask, mode, s)));
-    DAWN_TRY((launch_emit_t<7, 8>(ctx, a, 0, d_emask, mode, s)));
-    DAWN_TRY((launch_emit_t<15, 4>(ctx, a, 0, d_emask, mode, s)));
-    return launch_emit_t<16, 2>(ctx, a, 0, d_emask, mode, s);
+    if (a.nplanes >= 4) DAWN_TRY((launch_emit_t<7, 8>(ctx, a, 0, d_emask, mode, s)));
+    if (a.nplanes >= 8) DAWN_TRY((launch_emit_t<15, 4>(ctx, a, 0, d_emask, mode, s)));
+    if (a.nplanes >= 16) DAWN_TRY((launch_emit_t<16, 2>(ctx, a, 0, d_emask, mode, s)));
+    return DAWN_OK;
   }
   const int D = nplanes_used;
   if (D <= 3) return launch_emit_t<3, 16>(ctx, a, D, d_emask, mode, s);
@@ -1682,37 +1701,36 @@ static int bit_length(int x) {
 }
 
 // The prepare step's list: the control block first, then every array a run
-// writes, whole (an earlier run may have used a wider row stride).
-static ZeroList prepare_list(const GraphRec* g, const BatchWs* w) {
+// writes, whole (an earlier run may have used a wider row stride).  A one-launch
+// run has a control block of its own.
+static dawn_status batch_launch_prepare(Ctx* ctx, const GraphRec* g, BatchWs* w, bool fused,
+                                        bool clear_status, hipStream_t s) {
+  static_assert(12 + kMaxPlanes <= kZeroMax, "prepare list too long");
   ZeroList z;
   memset(&z, 0, sizeof(z));
   auto add = [&z](void* p, size_t count) {
     z.p[z.k] = (u64*)p;
     z.count[z.k++] = count;
   };
-  const size_t nW = (size_t)g->n * (size_t)w->Wmax;
-  const size_t nwords = ((size_t)g->n + 63) / 64;
+  const size_t n = (size_t)g->n;
+  const size_t nW = n * (size_t)w->Wmax;
+  const size_t nwords = (n + 63) / 64;
   add(w->ctrl, sizeof(BatchCtrl) / 8);
+  if (fused) add(w->fused, sizeof(FusedCtrl) / 8);
+  const int always = z.k;
+  add(w->touched[0], nwords);
+  add(w->touched[1], nwords);
+  const int second = z.k;
   add(w->vis, nW);
   add(w->nxt[0], nW);
   add(w->nxt[1], nW);
-  add(w->touched[0], nwords);
-  add(w->touched[1], nwords);
-  add(w->fmap[0], (size_t)g->n);
-  add(w->fmap[1], (size_t)g->n);
-  add(w->vmap, (size_t)g->n);
+  add(w->fmap[0], n);
+  add(w->fmap[1], n);
+  add(w->vmap, n);
   for (int b = 0; b < w->nplanes; ++b) add(w->planes[b], nW);
-  return z;
-}
-
-static dawn_status batch_launch_prepare(Ctx* ctx, const GraphRec* g, BatchWs* w, bool clear_status,
-                                        hipStream_t s) {
-  static_assert(9 + kMaxPlanes <= kZeroMax, "prepare list too long");
-  const ZeroList z = prepare_list(g, w);
-  const size_t most = (size_t)g->n * (size_t)w->Wmax;
   const int gx = (int)std::max<size_t>(
-      1, std::min<size_t>((most + kBatchBlock - 1) / kBatchBlock, (size_t)ctx->num_cu * 4));
-  hipLaunchKernelGGL(batch_prepare, dim3(gx), dim3(kBatchBlock), 0, s, z, w->flags,
+      1, std::min<size_t>((nW + kBatchBlock - 1) / kBatchBlock, (size_t)ctx->num_cu * 4));
+  hipLaunchKernelGGL(batch_prepare, dim3(gx), dim3(kBatchBlock), 0, s, z, always, second, w->flags,
                      clear_status ? 1 : 0);
   DAWN_HIP(hipGetLastError());
   return DAWN_OK;
@@ -1745,21 +1763,38 @@ struct BatchJob {
   int Lend = 0;     // last level of the chunk in flight
   int chunk = 4;
   int launches = 0;
+  bool fused = false;   // all levels in one launch
   bool done = false;
 };
 
 static dawn_status batch_begin(Ctx* ctx, const GraphRec* g, BatchJob& j, const int32_t* h_src,
-                               int k) {
+                               int k, bool alone) {
   BatchWs* w = j.w;
   j.k = k;
   j.W = (k + 63) / 64;
   hipStream_t s = w->stream;
   DAWN_HIP(hipMemcpyAsync(w->src, h_src, (size_t)k * 4, hipMemcpyHostToDevice, s));
   DAWN_HIP(hipEventRecord(w->ev0, s));
-  DAWN_TRY(batch_launch_prepare(ctx, g, w, true, s));
+  // A one-launch run holds its compute units to its end, so not beside other
+  // batches: all pairs of 12,463 nodes (three batches of 4096 and one of 175) took
+  // 1.92 to 2.40 ms with the last in one launch, 1.87 to 1.97 without.
+  j.fused = alone && batch_session_fits(g, *j.p, k);
+  if (j.fused) {
+    // planes for as many levels as the graph's last run had
+    const int hint = g->batch_hint.load(std::memory_order_relaxed);
+    DAWN_TRY(batch_ensure_planes(w, std::max(bit_length(hint), 3), j.W));
+  }
+  DAWN_TRY(batch_launch_prepare(ctx, g, w, j.fused, true, s));
   j.a = batch_args(g, w, j.W);
   batch_knobs(j.a, *j.p);
   set_rows(j.a, j.row_base, j.row_stride, k);
+  j.done = false;
+  if (j.fused) {
+    j.a.fused = 1;
+    DAWN_TRY(batch_session_seed_launch(j.a, w->fused, w->src, k, s));
+    j.launches = 2;
+    return DAWN_OK;
+  }
   DAWN_TRY(batch_launch_seed(ctx, j.a, w->src, nullptr, k, 0, false, s));
   DAWN_TRY(batch_launch_merge(ctx, j.a, 0, s));
   j.launches = 3;
@@ -1770,6 +1805,30 @@ static dawn_status batch_begin(Ctx* ctx, const GraphRec* g, BatchJob& j, const i
   return DAWN_OK;
 }
 
+// A one-launch run: its levels, the emission (gated on their having finished)
+// and the run state's way back.  A run that stopped for want of level planes
+// goes on here with more of them.
+static dawn_status session_enqueue(Ctx* ctx, const GraphRec* g, BatchJob& j) {
+  BatchWs* w = j.w;
+  hipStream_t s = w->stream;
+  if (j.launches > 2) {
+    const int need = std::min(w->nplanes + 2, kMaxPlanes);
+    if (need == w->nplanes)
+      return fail(DAWN_E_DEVICE, "batched traversal exceeds %d levels", (1 << kMaxPlanes) - 1);
+    DAWN_TRY(batch_ensure_planes(w, need, j.W));
+    for (int b = 0; b < w->nplanes; ++b) j.a.planes[b] = w->planes[b];
+    j.a.nplanes = w->nplanes;
+    DAWN_TRY(batch_launch_zero(ctx, (u64*)&w->fused->sess, sizeof(SessCtrl) / 8, s));
+  }
+  DAWN_TRY(batch_session_launch(ctx, j.a, w->fused, s));
+  DAWN_TRY(batch_launch_emit(ctx, j.a, 0, nullptr, kEmitClear | kEmitFromRun | kEmitMarkClean, s));
+  DAWN_HIP(hipEventRecord(w->ev1, s));
+  DAWN_HIP(hipMemcpyAsync(&w->h_ctrl->run, &w->ctrl->run, sizeof(BatchRun), hipMemcpyDeviceToHost, s));
+  DAWN_HIP(hipMemcpyAsync(w->h_part, w->fused->part, sizeof(w->fused->part), hipMemcpyDeviceToHost, s));
+  j.launches += 2;
+  return DAWN_OK;
+}
+
 // Levels go out in chunks without a host round trip: batch_control picks
 // each level's direction on the device and stops the run, after which the
 // chunk's remaining launches return at once.  The host reads the run state
@@ -1777,6 +1836,7 @@ static dawn_status batch_begin(Ctx* ctx, const GraphRec* g, BatchJob& j, const i
 static dawn_status batch_enqueue(Ctx* ctx, const GraphRec* g, const dawn_params& p, BatchJob& j) {
   BatchWs* w = j.w;
   hipStream_t s = w->stream;
+  if (j.fused) return session_enqueue(ctx, g, j);
   const int L = j.L;
   if (L > g->n + 1) return fail(DAWN_E_DEVICE, "watchdog: more than n levels");
   if (bit_length(L) > kMaxPlanes)
@@ -1810,7 +1870,9 @@ static dawn_status batch_check(BatchJob& j) {
     j.done = true;
     return DAWN_OK;
   }
+  if (j.fused && r.done == 4) return DAWN_OK;     // more planes, then on
   if (r.done) return fail(DAWN_E_DEVICE, "batched level loop stopped (watchdog)");
+  if (j.fused) return fail(DAWN_E_DEVICE, "batched level loop did not finish");
   j.L = j.Lend + 1;
   j.chunk = std::min(j.chunk * 2, 64);
   return DAWN_OK;
@@ -1818,7 +1880,13 @@ static dawn_status batch_check(BatchJob& j) {
 
 static dawn_status batch_finish(Ctx* ctx, const GraphRec* g, BatchJob& j, BatchTotals* tot) {
   BatchWs* w = j.w;
-  const BatchRun run = w->h_ctrl->run;
+  BatchRun run = w->h_ctrl->run;
+  if (j.fused)
+    for (int i = 0; i < kStripes; ++i) {
+      run.edges += w->h_part[i].edges;
+      run.reached += w->h_part[i].reached;
+      run.source_edges += w->h_part[i].degs;
+    }
   tot->edges += run.edges;
   tot->reached += run.reached;
   tot->source_edges += run.source_edges;
@@ -1827,11 +1895,13 @@ static dawn_status batch_finish(Ctx* ctx, const GraphRec* g, BatchJob& j, BatchT
   const int last_nonempty = run.last_nonempty;
   // expansions 1 .. last_nonempty + 1, then the control step that ends the run
   g->batch_hint.store(std::min(last_nonempty + 2, 64), std::memory_order_relaxed);
-  // every lane is emitted and its bits cleared: the workspace is left clear
-  DAWN_TRY(batch_launch_emit(ctx, j.a, bit_length(last_nonempty), nullptr,
-                             kEmitClear | kEmitMarkClean, w->stream));
-  j.launches += 1;
-  DAWN_HIP(hipEventRecord(w->ev1, w->stream));
+  if (!j.fused) {
+    // every lane is emitted and its bits cleared: the workspace is left clear
+    DAWN_TRY(batch_launch_emit(ctx, j.a, bit_length(last_nonempty), nullptr,
+                               kEmitClear | kEmitMarkClean, w->stream));
+    j.launches += 1;
+    DAWN_HIP(hipEventRecord(w->ev1, w->stream));
+  }
   tot->launches += j.launches;
   tot->levels = std::max(tot->levels, last_nonempty + 1);
   return DAWN_OK;
@@ -1949,7 +2019,7 @@ dawn_status mssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, const int32_t*
       j.row_base = device_out ? dist + (size_t)b0 * row_stride : stage + (size_t)b0 * g->n;
       j.row_stride = device_out ? row_stride : g->n;
       j.p = &p;
-      st = batch_begin(ctx, g, j, sources + b0, kb);
+      st = batch_begin(ctx, g, j, sources + b0, kb, nj == 1);
     }
     // chunks of levels, all running batches side by side
     for (bool busy = true; busy && st == DAWN_OK;) {
@@ -2060,6 +2130,18 @@ static dawn_status launch_finish(Ctx* ctx, const BatchArgs& a, u64* act, int L0,
   }
 }
 
+// After a device-ordered one-launch run: one that stopped for want of planes or
+// whose barrier timed out has failed.
+__global__ void session_verdict(BatchRun* run, unsigned* flags) {
+  const int d = run->done;
+  if (d == 0 || d == 4) atomicMax(&flags[kFlagStatus], 2u);
+}
+static dawn_status batch_session_verdict(const BatchArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(session_verdict, dim3(1), dim3(1), 0, s, &a.ctrl->run, a.flags);
+  DAWN_HIP(hipGetLastError());
+  return DAWN_OK;
+}
+
 // Levels queued as separate launches before the cooperative tail takes over.
 constexpr int kDeviceHintMax = 256;
 
@@ -2104,10 +2186,20 @@ dawn_status mssp_device_run(Ctx* ctx, GraphRec* g, const dawn_params& p, const i
   for (int64_t b0 = 0; b0 < k && st == DAWN_OK; b0 += lanes) {
     const int kb = (int)std::min<int64_t>(lanes, k - b0);
     const int W = (kb + 63) / 64;
-    st = batch_launch_prepare(ctx, g, w, false, s);
+    const bool fused = batch_session_fits(g, p, kb);
+    st = batch_launch_prepare(ctx, g, w, fused, false, s);
     BatchArgs a = batch_args(g, w, W);
     batch_knobs(a, p);
     set_rows(a, d_dist + (size_t)b0 * g->n, g->n, kb);
+    if (fused) {
+      a.fused = 1;
+      if (st == DAWN_OK) st = batch_session_seed_launch(a, w->fused, d_src + b0, kb, s);
+      if (st == DAWN_OK) st = batch_session_launch(ctx, a, w->fused, s);
+      if (st == DAWN_OK) st = batch_session_verdict(a, s);
+      if (st == DAWN_OK)
+        st = batch_launch_emit(ctx, a, 0, nullptr, kEmitClear | kEmitFromRun | kEmitMarkClean, s);
+      continue;
+    }
     if (st == DAWN_OK) st = batch_launch_seed(ctx, a, d_src + b0, nullptr, kb, 0, false, s);
     if (st == DAWN_OK) st = batch_launch_merge(ctx, a, 0, s);
     for (int l = 1; l <= hint && st == DAWN_OK; ++l) {
