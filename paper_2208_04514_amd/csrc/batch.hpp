@@ -117,8 +117,9 @@ struct BatchArgs {
   int32_t big_b;                // push: out-degree from which a node's edges go by chunks
   int32_t wide_scan;            // narrow rows: in-list length scanned by the whole wave
   int32_t sparse_words;         // push one edge per lane for nodes with <= this many words
-  int32_t fused;                // a one-launch run's rows: the emission takes the buffer
-                                //   ctrl->run.vis_buf names
+  int32_t fused;                // 1: a one-launch run's rows: the emission takes the buffer
+                                //   ctrl->run.vis_buf names; 2: one-pass levels' rows: in
+                                //   vis, those of the level before in nxt[0]
   unsigned* flags;              // [0] the workspace may hold bits (set by the seed, cleared by
                                 //   a complete emission), [1] run status: 0 ok, 1 invalid
                                 //   source, 2 watchdog (device-ordered calls report it)
@@ -209,6 +210,26 @@ dawn_status batch_launch_control(const BatchArgs& a, u64* act, int L, const dawn
                                  hipStream_t s);
 dawn_status batch_launch_seed(Ctx* ctx, const BatchArgs& a, const int32_t* d_src,
                               const int32_t* d_lane, int k, int L, bool live, hipStream_t s);
+// One-pass levels (served batches of at most kStepWords words): whether a batch
+// of W words takes them; a level, from the rows a.vis to out; the step before it;
+// sources that join; and their end while lanes are running (from_nxt: the rows are
+// in nxt[0]; the next level pulls, as there is no frontier).
+constexpr int kStepWords = 16;
+constexpr int kStepNodes = 400000;  // on more nodes than this they start with at least
+constexpr int kStepSources = 16;    //   this many sources
+constexpr int kStepQueries = 64;    // queries whose end a queued level looks for
+constexpr int kStepAhead = 8;       // levels queued at a time, from this many row words on
+constexpr long long kStepAheadWords = 128 << 10;
+bool batch_step_fits(const GraphRec* g, const dawn_params& p, int W);
+dawn_status batch_launch_step(Ctx* ctx, const BatchArgs& a, u64* out, int L, bool sparse,
+                              const unsigned* stop, hipStream_t s);
+dawn_status batch_launch_step_control(const BatchArgs& a, const BatchActWords& act, u64* d_act,
+                                      int L, bool first, const u64* d_qmask, int nq,
+                                      hipStream_t s);
+dawn_status batch_launch_step_seed(const BatchArgs& a, const int32_t* d_src, const int32_t* d_lane,
+                                   int k, hipStream_t s);
+dawn_status batch_launch_step_leave(Ctx* ctx, const BatchWs* w, int Ws, bool from_nxt,
+                                    hipStream_t s);
 // One-launch runs (bsession.hip): whether k sources take one.
 bool batch_session_fits(const GraphRec* g, const dawn_params& p, int k);
 dawn_status batch_session_seed_launch(const BatchArgs& a, FusedCtrl* fc, const int32_t* d_src,

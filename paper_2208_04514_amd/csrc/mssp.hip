@@ -897,6 +897,308 @@ __global__ __launch_bounds__(kBatchBlock) void batch_merge(BatchArgs a, int L) {
   if (batch_gate_open(a, -1)) merge_level<P>(a, L);
 }
 
+// ---------------------------------------------------------- one-pass level --
+// A served level of at most 16 words: pull and merge in one pass, between two
+// buffers of visited rows used in turn (a.vis and out), so that nobody reads a
+// bit of the level being run:
+//
+//   new[v] = act & ~vis[v] & OR over in-neighbours u of vis[u];  out[v] = vis[v] | new[v]
+//
+// The lanes that own a node write its row whole and, where new is not empty, its
+// level planes; there is no frontier to list, to read again and to clear.  A long
+// in-list's chunks OR into out, whose row is that of two levels ago, a subset.
+// sparse: few rows are nonzero yet, so a neighbour's word map is read first.
+//
+// What bounds it: the planes (3.5 atomic ORs per new word at 130 levels, 2.2 ms of
+// a burst's 10) and the chain list bounds -> in-list -> row, hence two nodes at a
+// time per lane group.  12 queries of 1 to 512 sources on the 512 x 512 grid, 12 on
+// R-MAT of 65K nodes: 17.6 ms with push or pull, then merge (47 + 71 us a level on
+// the grid); 11.7 with this pass (35 to 75); 9.6 with several levels queued (see
+// batch_step_control).  Reading only words that changed at the last level, by a
+// map per node, measured the same, as did a row stride of 16 words.
+template <int P>
+__global__ __launch_bounds__(kBatchBlock) void batch_step(BatchArgs a, u64* out, int L, int sparse,
+                                                          const unsigned* stop) {
+  __shared__ u64 lmask[kMaxPlanes][P];    // bit b of (L - base) for the lanes of each word
+  __shared__ u64 actb[P];
+  __shared__ unsigned fresh;             // rows that became nonzero
+  if (ld_relaxed(&a.ctrl->run.done)) return;
+  // the host's wish to end the queued levels, read while the level runs
+  unsigned asked = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    asked = __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  constexpr int NPW = kWave / P;
+  constexpr int U = 2;
+  const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+  const int D = a.nplanes;
+  for (int x = wv; x < a.W; x += kBatchBlock / kWave) {
+    const int rel = L - a.base[x * 64 + lane];
+#pragma unroll
+    for (int b = 0; b < kMaxPlanes; ++b) {
+      const u64 m = __ballot(b < D && ((rel >> b) & 1));
+      if (lane == 0) lmask[b][x] = m;
+    }
+  }
+  if (tid < P) actb[tid] = 0;
+  if (tid == 0) fresh = 0;
+  __syncthreads();
+  const int w = lane & (P - 1), sub = lane / P, gb = lane & ~(P - 1);
+  const bool wok = w < a.W;
+  const u64 gm = group_mask<P>(lane);
+  const u64 actw = wok ? a.act[w] : 0ull;
+  const size_t Ws = (size_t)a.Ws;
+  const u64* vis = a.vis;
+  const u64* fm = a.vmap;
+  const unsigned gw = (blockIdx.x * kBatchBlock + tid) / kWave;
+  const unsigned nwaves = gridDim.x * kBatchBlock / kWave;
+  u64 act_acc = 0;
+  unsigned nfresh = 0;
+
+  // new bits of word x of node v (idx: its place in the rows)
+  auto planes_or = [&](size_t idx, int x, u64 bits) {
+    for (int b = 0; b < D; ++b) {
+      const u64 m = lmask[b][x] & bits;
+      if (m) atom_or(&a.planes[b][idx], m);
+    }
+  };
+  // a chunk's find: the first chunk to set a bit records it
+  auto chunk_done = [&](int v, int x, u64 old, u64 got) {
+    if (!(old | got)) return;
+    const size_t idx = (size_t)v * Ws + x;
+    const u64 nb = got & ~atom_or(&out[idx], old | got);
+    if (!nb) return;
+    planes_or(idx, x, nb);
+    atom_or(&a.vmap[v], 1ull << x);
+    atomicOr(&actb[x], nb);
+  };
+  // wide groups: one list, a part of it per group of the wave (need: word w's)
+  auto split_scan = [&](int s, int e, u64 need) -> u64 {
+    const int part = (e - s + NPW - 1) / NPW;
+    const int s0 = min(s + sub * part, e);
+    u64 got = 0;
+    pull_scan<P>(a, vis, fm, s0, min(s0 + part, e), need, w, gb, gm, got);
+    for (int off = P; off < kWave; off <<= 1) got |= shfl_xor64(got, off);
+    return got;
+  };
+  for (unsigned c = gw; c < (unsigned)a.npc; c += nwaves) {
+    const int v = a.pcv[c];
+    const int s = a.ip[v] + a.pck[c] * kPullChunk;
+    const int e = min(s + kPullChunk, a.ip[v + 1]);
+    const u64 old = wok ? vis[(size_t)v * Ws + w] : 0ull;
+    const u64 need = actw & ~old;
+    u64 got = 0;
+    if (__ballot(need != 0)) {
+      if constexpr (P <= 8) {
+        u64 needw[P], accw[P];
+#pragma unroll
+        for (int x = 0; x < P; ++x) {
+          needw[x] = shfl64(need, x);
+          accw[x] = 0;
+        }
+        wave_scan<P>(a, vis, fm, s, e, needw, accw);
+#pragma unroll
+        for (int x = 0; x < P; ++x)
+          if (x == lane) got = accw[x];
+      } else {
+        got = split_scan(s, e, need);
+      }
+    }
+    if (wok && sub == 0) chunk_done(v, w, old, got);
+  }
+
+  const unsigned units = (unsigned)((a.n + NPW - 1) / NPW);
+  for (unsigned un = gw; un < units; un += U * nwaves) {
+    int v[U], s[U], e[U], j[U];
+    bool mine[U], wide[U], go[U];
+    u64 vw[U], acc[U], need[U];
+    bool any_go = false;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const unsigned x = un + (unsigned)k * nwaves;
+      v[k] = (int)x * NPW + sub;
+      mine[k] = x < units && v[k] < a.n;
+      s[k] = e[k] = 0;
+      vw[k] = 0;
+      if (mine[k]) {
+        s[k] = a.ip[v[k]];
+        e[k] = a.ip[v[k] + 1];
+        if (wok) vw[k] = vis[(size_t)v[k] * Ws + w];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      mine[k] = mine[k] && e[k] - s[k] < kPullBig;     // long in-lists went by chunks
+      need[k] = mine[k] ? actw & ~vw[k] : 0ull;
+      const bool wanted = (__ballot(need[k] != 0) & gm) != 0;
+      wide[k] = wanted && e[k] - s[k] > a.wide_scan;
+      acc[k] = 0;
+      j[k] = s[k];
+      go[k] = wanted && !wide[k] && s[k] < e[k];
+      any_go = any_go || go[k];
+    }
+    while (__ballot(any_go)) {
+      int uu[U][4];
+      u64 val[U][4];
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) uu[k][q] = go[k] && j[k] + q < e[k] ? a.isrc[j[k] + q] : -1;
+      if (sparse) {
+        u64 m[U][4];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) m[k][q] = uu[k][q] >= 0 ? fm[uu[k][q]] : 0ull;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (!((m[k][q] >> w) & 1ull)) uu[k][q] = -1;
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          val[k][q] = uu[k][q] >= 0 && wok ? vis[(size_t)uu[k][q] * Ws + w] : 0ull;
+      any_go = false;
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        acc[k] |= (val[k][0] | val[k][1] | val[k][2] | val[k][3]) & need[k];
+        j[k] += 4;
+        const bool more = (__ballot(acc[k] != need[k]) & gm) != 0;
+        go[k] = go[k] && more && j[k] < e[k];
+        any_go = any_go || go[k];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      u64 lead = __ballot(wide[k] && w == 0);
+      while (lead) {
+        const int ld = __ffsll((unsigned long long)lead) - 1;
+        lead &= lead - 1;
+        const int ss = __builtin_amdgcn_readlane(s[k], ld);
+        const int ee = __builtin_amdgcn_readlane(e[k], ld);
+        if constexpr (P <= 8) {
+          u64 needw[P], accw[P];
+#pragma unroll
+          for (int x = 0; x < P; ++x) {
+            needw[x] = shfl64(need[k], ld + x);
+            accw[x] = 0;
+          }
+          wave_scan<P>(a, vis, fm, ss, ee, needw, accw);
+#pragma unroll
+          for (int x = 0; x < P; ++x)
+            if (lane == ld + x) acc[k] = accw[x];
+        } else {
+          const u64 got = split_scan(ss, ee, shfl64(need[k], ld + w));
+          if (gb == ld) acc[k] = got;
+        }
+      }
+      if (mine[k] && wok) {
+        const size_t idx = (size_t)v[k] * Ws + w;
+        out[idx] = vw[k] | acc[k];
+        if (acc[k]) {
+          planes_or(idx, w, acc[k]);
+          act_acc |= acc[k];
+        }
+      }
+      const u64 was = __ballot(vw[k] != 0) & gm;
+      const u64 first = __ballot(acc[k] != 0 && vw[k] == 0) & gm;   // words no longer empty
+      if (first && w == 0) {
+        atom_or(&a.vmap[v[k]], first >> gb);
+        if (!was) nfresh += 1;
+      }
+    }
+  }
+  if (act_acc) atomicOr(&actb[w], act_acc);
+  nfresh = wave_sum(nfresh);
+  if (lane == 0 && nfresh) atomicAdd(&fresh, nfresh);
+  __syncthreads();
+  const int cl = L & 1, stripe = blockIdx.x % kStripes;
+  if (tid < a.W && actb[tid]) {
+    u64* gp = &a.ctrl->laneact[cl][stripe][tid];
+    if (actb[tid] & ~ld_relaxed(gp)) atom_or(gp, actb[tid]);
+  }
+  if (tid == 0 && fresh) atom_add(&a.ctrl->lv[cl].s[stripe].nodes, (u64)fresh);
+  if (asked) a.ctrl->lv[cl].nchunks = 1;
+}
+
+// Before one-pass level L.  Several are queued at a time (the round trip to the
+// host between two levels takes 40 us, as long as the level); the first takes
+// its active lanes from the host, a later one those that found something at the
+// level before.  The rest stand down (run.done) once a query has no active lane
+// left, its rows being due (query i: lanes qmask[i * kStepWords + w]), and when
+// the host asks (a query waits to join; the level before noted it in the slot's
+// nchunks, otherwise unused here).  A level's counters stay in its slot when it
+// was the last.
+__global__ __launch_bounds__(kWave) void batch_step_control(BatchArgs a, BatchActWords act,
+                                                           u64* d_act, int L, int first,
+                                                           const u64* qmask, int nq) {
+  __shared__ u64 st[kWave];
+  const int lane = lane_id();
+  BatchRun* r = &a.ctrl->run;
+  if (first) {
+    if (lane < act.W) d_act[lane] = act.w[lane];
+    if (lane == 0) {
+      r->done = 0;
+      r->pull_levels = 1;
+      r->reached = 0;
+      a.ctrl->emit_next = 0;
+    }
+  } else {
+    if (ld_relaxed(&r->done)) return;
+    const int prev = (L - 1) & 1;
+    const unsigned asked = a.ctrl->lv[prev].nchunks;
+    const u64 nodes = wave_sum(lane < kStripes ? a.ctrl->lv[prev].s[lane].nodes : (u64)0);
+    u64 still = 0;
+    for (int i = 0; i < kStripes; ++i)
+      if (lane < a.W) still |= a.ctrl->laneact[prev][i][lane];
+    st[lane] = still;
+    __builtin_amdgcn_wave_barrier();
+    bool over = asked != 0;
+    if (lane < nq) {
+      u64 x = 0;
+      for (int w = 0; w < a.W; ++w) x |= st[w] & qmask[lane * kStepWords + w];
+      over = over || x == 0;
+    }
+    if (__ballot(over)) {
+      if (lane == 0) r->done = 1;
+      return;
+    }
+    if (lane < a.W) d_act[lane] = still;
+    if (lane == 0) {
+      r->pull_levels += 1;
+      r->reached += nodes;
+    }
+  }
+  const int cl = L & 1;
+  for (int i = lane; i < kStripes * 64; i += kWave) a.ctrl->laneact[cl][i / 64][i % 64] = 0;
+  if (lane < kStripes) a.ctrl->lv[cl].s[lane].nodes = 0;
+  if (lane == 0) a.ctrl->lv[cl].nchunks = 0;
+}
+
+// Source i, lane lane[i], joins one-pass levels: its bit in its row.
+__global__ void batch_step_seed(BatchArgs a, const int32_t* src, const int32_t* lane, int k) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= k || (unsigned)src[i] >= (unsigned)a.n) return;
+  const int s = src[i], l = lane[i];
+  atom_or(&a.vis[(size_t)s * a.Ws + (l >> 6)], 1ull << (l & 63));
+  atom_or(&a.vmap[s], 1ull << (l >> 6));
+}
+
+// One-pass levels end with lanes still running: their rows go to vis, and the
+// other buffer becomes the (empty) new bits of an expansion again.
+__global__ __launch_bounds__(kBatchBlock) void batch_step_leave(u64* vis, u64* nxt, int from_nxt,
+                                                               long long n, int Ws, int W) {
+  const size_t total = (size_t)n * W;
+  for (size_t i = blockIdx.x * (size_t)kBatchBlock + threadIdx.x; i < total;
+       i += (size_t)gridDim.x * kBatchBlock) {
+    const size_t idx = i / W * Ws + i % W;
+    if (from_nxt) vis[idx] = nxt[idx];
+    nxt[idx] = 0;
+  }
+}
+
 // ------------------------------------------------------------------ emit --
 // Write the distance rows of the lanes in emask.  A wave takes a task of 64
 // nodes (lane l owns node v0 + l) and a group of EG consecutive words of their
@@ -964,10 +1266,13 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
     D = min(bit_length_dev(ld_relaxed(&r.last_nonempty)), a.nplanes);
     if (D < emit_dmin<DMAX>() || D > DMAX) return;
   }
-  // a one-launch run ends in either of its row buffers; both are cleared
-  const bool swapped = a.fused && ld_relaxed(&a.ctrl->run.vis_buf);
+  // a one-launch run ends in either of its row buffers; both are cleared (the
+  // other one of one-pass levels, too, holds no bit that a.vis does not)
+  const bool swapped = a.fused == 1 && ld_relaxed(&a.ctrl->run.vis_buf);
   u64* const visp = swapped ? a.nxt[0] : a.vis;
-  u64* const other = a.fused && (mode & kEmitMarkClean) ? (swapped ? a.vis : a.nxt[0]) : nullptr;
+  u64* const other = a.fused == 2 ? a.nxt[0]
+                     : a.fused && (mode & kEmitMarkClean) ? (swapped ? a.vis : a.nxt[0])
+                                                          : nullptr;
   if ((mode & kEmitMarkClean) && blockIdx.x == 0 && threadIdx.x == 0)
     a.flags[kFlagDirty] = a.fused ? 2u : 0u;
   // the row pointers of all lanes, staged once: a per-word global load in the
@@ -1097,7 +1402,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_emit(BatchArgs a, int D,
       if (clear && live && !cleared) {
         const u64 rem = xe & ~em;
         visp[base + e] = rem;
-        if (other) other[base + e] = 0;
+        if (other) other[base + e] = a.fused == 2 ? other[base + e] & ~em : 0;
 #pragma unroll
         for (int d = 0; d < DMAX; ++d)
           if (d < D) a.planes[d][base + e] = pe[d] & ~em;
@@ -1590,6 +1895,59 @@ dawn_status batch_launch_merge(Ctx* ctx, const BatchArgs& a, int L, hipStream_t 
     default: return fail(DAWN_E_INVALID_ARG, "batch too wide");
   }
 #undef DAWN_MERGE
+  DAWN_HIP(hipGetLastError());
+  return DAWN_OK;
+}
+
+// One-pass levels against push or pull, then merge; a query alone, us:
+//  * 100 sources: R-MAT of 66K nodes and 1.8M edges 347 / 555, of 262K and 7.6M 673 /
+//    879; uniform of 1M and 8.4M 2538 / 3383; 1024 x 1024 grid 19355 / 28228;
+//  * 1000 sources: uniform of 262K and 4.2M 1564 / 1719, R-MAT of 262K and 7.6M 1902 /
+//    1908: there the gain ends, and R-MAT of 1M and 31M is left to the others;
+//  * few sources, whose first levels touch few nodes: 1 source on uniform of 262K
+//    428 / 585, on R-MAT of 524K and 8M 701 / 686; eight queries of 1 on uniform of
+//    1M 3187 / 4137, alone 1861 / 1470: from 400K nodes on such a batch starts with
+//    pushes.
+bool batch_step_fits(const GraphRec* g, const dawn_params& p, int W) {
+  return W <= kStepWords && p.direction != 1 && g->m <= std::max(8ll << 20, 20ll * g->n);
+}
+
+dawn_status batch_launch_step(Ctx* ctx, const BatchArgs& a, u64* out, int L, bool sparse,
+                              const unsigned* stop, hipStream_t s) {
+  const int grid = ctx->num_cu * 8, sp = sparse ? 1 : 0;
+  const dim3 gd(grid), bd(kBatchBlock);
+  switch (pow2_at_least(a.W)) {
+    case 1: hipLaunchKernelGGL(batch_step<1>, gd, bd, 0, s, a, out, L, sp, stop); break;
+    case 2: hipLaunchKernelGGL(batch_step<2>, gd, bd, 0, s, a, out, L, sp, stop); break;
+    case 4: hipLaunchKernelGGL(batch_step<4>, gd, bd, 0, s, a, out, L, sp, stop); break;
+    case 8: hipLaunchKernelGGL(batch_step<8>, gd, bd, 0, s, a, out, L, sp, stop); break;
+    case 16: hipLaunchKernelGGL(batch_step<16>, gd, bd, 0, s, a, out, L, sp, stop); break;
+    default: return fail(DAWN_E_INVALID_ARG, "batch too wide for a one-pass level");
+  }
+  DAWN_HIP(hipGetLastError());
+  return DAWN_OK;
+}
+
+dawn_status batch_launch_step_control(const BatchArgs& a, const BatchActWords& act, u64* d_act,
+                                      int L, bool first, const u64* d_qmask, int nq,
+                                      hipStream_t s) {
+  hipLaunchKernelGGL(batch_step_control, dim3(1), dim3(kWave), 0, s, a, act, d_act, L,
+                     first ? 1 : 0, d_qmask, nq);
+  DAWN_HIP(hipGetLastError());
+  return DAWN_OK;
+}
+
+dawn_status batch_launch_step_seed(const BatchArgs& a, const int32_t* d_src, const int32_t* d_lane,
+                                   int k, hipStream_t s) {
+  hipLaunchKernelGGL(batch_step_seed, dim3((k + 255) / 256), dim3(256), 0, s, a, d_src, d_lane, k);
+  DAWN_HIP(hipGetLastError());
+  return DAWN_OK;
+}
+
+dawn_status batch_launch_step_leave(Ctx* ctx, const BatchWs* w, int Ws, bool from_nxt,
+                                    hipStream_t s) {
+  hipLaunchKernelGGL(batch_step_leave, dim3(ctx->num_cu * 8), dim3(kBatchBlock), 0, s, w->vis,
+                     w->nxt[0], from_nxt ? 1 : 0, (long long)w->n, Ws, std::min(Ws, kStepWords));
   DAWN_HIP(hipGetLastError());
   return DAWN_OK;
 }

@@ -14,7 +14,9 @@
 //        enough lanes are free and the HBM budget allows: their sources are
 //        seeded at the current level, with base = that level, so they join the
 //        running batch mid-flight (a source's distance is level - base);
-//     3. the next level is launched if any lane is still expanding.
+//     3. the next level is launched if any lane is still expanding; of levels that
+//        take one pass (batches of at most 16 words) several, the rest of which
+//        stand down as soon as 1 or 2 has something to do.
 //
 // Engines of different graphs overlap on the device; the thread polls their
 // events instead of blocking on one.  Timestamps: submit, admit, done.
@@ -69,6 +71,16 @@ struct Engine {
   int busy_count = 0;
   BatchLevelSum last{};
   bool have_last = false;
+  // one-pass levels (batch_launch_step): the rows are in vis or (buf 1) nxt[0]
+  bool steps = false;
+  int buf = 0;
+  u64 fresh_rows = 0;              // rows that became nonzero since the engine was idle
+  int ahead = 1;                   // levels to queue at a time
+  int queued = 0;                  // levels in flight
+  unsigned* h_stop = nullptr;      // pinned: the levels in flight shall end
+  u64* h_qmask = nullptr;          // pinned: lanes of each running query
+  int nq = -1;                     // queries in it (-1: out of date)
+  u64* rows(bool other) const { return (buf != 0) != other ? ws->nxt[0] : ws->vis; }
   // pinned host mirrors of what is copied to the device at a level boundary
   // (a boundary's copies have finished before the next boundary starts)
   int32_t** h_rows = nullptr;
@@ -131,7 +143,7 @@ static void engine_destroy_raw(Engine* e) {
   }
   if (e->lev_ev) hipEventDestroy(e->lev_ev);
   for (void* p : {(void*)e->h_rows, (void*)e->h_base, (void*)e->h_src, (void*)e->h_lane,
-                  (void*)e->h_em})
+                  (void*)e->h_em, (void*)e->h_stop, (void*)e->h_qmask})
     if (p) hipHostFree(p);
   delete e;
 }
@@ -170,6 +182,8 @@ static dawn_status engine_create(Server* S, const std::shared_ptr<GraphRec>& g, 
   if (he == hipSuccess) he = hipHostMalloc((void**)&e->h_src, 4096 * 4, 0);
   if (he == hipSuccess) he = hipHostMalloc((void**)&e->h_lane, 4096 * 4, 0);
   if (he == hipSuccess) he = hipHostMalloc((void**)&e->h_em, 64 * 8, 0);
+  if (he == hipSuccess) he = hipHostMalloc((void**)&e->h_stop, 64, 0);
+  if (he == hipSuccess) he = hipHostMalloc((void**)&e->h_qmask, kStepQueries * kStepWords * 8, 0);
   if (he == hipSuccess) {
     for (int i = 0; i < 4096; ++i) {
       e->h_rows[i] = nullptr;
@@ -270,6 +284,7 @@ static Query* admit(Server* S, Engine* e) {
       hi = std::max(hi, lane);
     }
     e->busy_count += k;
+    e->nq = -1;
     q->remaining = k;
     q->qs.admit_ns = now_ns();
     q->qs.batch_peak = std::max(q->qs.batch_peak, e->busy_count);
@@ -282,6 +297,13 @@ static Query* admit(Server* S, Engine* e) {
                    w->stream);
   }
   return mem_wait;
+}
+
+// Whether a queued query of this engine's graph fits its free lanes; S->mu held.
+static bool may_admit(const Server* S, const Engine* e) {
+  for (const Query* q : S->pending)
+    if (q->g.get() == e->g.get() && (int)q->src.size() <= e->capacity - e->busy_count) return true;
+  return false;
 }
 
 // Launch seeds (if any) and the next level of engine e.  S->mu held.
@@ -303,13 +325,30 @@ static dawn_status launch_level(Server* S, Engine* e) {
     std::lock_guard<std::mutex> lk(e->g->mu);
     p = e->g->params;
   }
+  // One-pass levels from an idle engine on (all arrays clear), until the batch
+  // gets too wide for them.
+  const bool narrow = batch_step_fits(g, p, Wa);
+  bool entered = false;
+  if (e->busy_count == e->nseed) {
+    e->steps = narrow && (g->n <= kStepNodes || e->busy_count >= kStepSources);
+    e->buf = 0;
+    e->fresh_rows = 0;
+  } else if (e->steps && !narrow) {
+    DAWN_TRY(batch_launch_step_leave(S->ctx, w, e->W, e->buf != 0, s));
+    e->steps = false;
+    entered = true;
+  }
   BatchArgs a = batch_args(g, w, e->W, Wa);
   batch_knobs(a, p);
+  if (e->steps) a.vis = e->rows(false);
   if (e->nseed > 0) {
     const int k = e->nseed;
     DAWN_HIP(hipMemcpyAsync(w->src, e->h_src, (size_t)k * 4, hipMemcpyHostToDevice, s));
     DAWN_HIP(hipMemcpyAsync(w->lane, e->h_lane, (size_t)k * 4, hipMemcpyHostToDevice, s));
-    DAWN_TRY(batch_launch_seed(S->ctx, a, w->src, w->lane, k, L, true, s));
+    if (e->steps)
+      DAWN_TRY(batch_launch_step_seed(a, w->src, w->lane, k, s));
+    else
+      DAWN_TRY(batch_launch_seed(S->ctx, a, w->src, w->lane, k, L, true, s));
     e->nseed = 0;
   }
   // planes for the largest relative level of the next step
@@ -319,16 +358,56 @@ static dawn_status launch_level(Server* S, Engine* e) {
   const int need = bit_length(L + 1 - min_base);
   if (need > w->nplanes) {
     DAWN_TRY(batch_ensure_planes(w, need, e->W));
-    a = batch_args(g, w, e->W, Wa);
-    batch_knobs(a, p);
+    for (int b = 0; b < kMaxPlanes; ++b) a.planes[b] = w->planes[b];
+    a.nplanes = w->nplanes;
   }
-  // the merge writes only the planes a running lane's level can reach
-  a.nplanes = std::min(a.nplanes, std::max(need, 1));
   BatchActWords aw;
   aw.W = e->W;
   for (int i = 0; i < 64; ++i) aw.w[i] = i < e->W ? e->act[i] : 0ull;
+  e->queued = 1;
+  if (e->steps) {
+    // several levels, as far as the planes there are go; the running queries'
+    // lanes in the place of the sources (seeded by now)
+    if (e->nq < 0) {
+      e->nq = 0;
+      memset(e->h_qmask, 0, kStepQueries * kStepWords * 8);
+      std::map<const Query*, int> at;
+      for (int lane = 0; lane < Wa * 64 && e->nq <= kStepQueries; ++lane) {
+        const Query* q = e->owner[lane];
+        if (!q) continue;
+        auto it = at.emplace(q, e->nq);
+        if (it.second && ++e->nq > kStepQueries) break;
+        e->h_qmask[it.first->second * kStepWords + (lane >> 6)] |= 1ull << (lane & 63);
+      }
+      DAWN_HIP(hipMemcpyAsync(w->src, e->h_qmask, kStepQueries * kStepWords * 8,
+                              hipMemcpyHostToDevice, s));
+    }
+    // (one at a time on small rows: a run of a few hundred such levels would be
+    // over, 3 ms on 128 x 128 nodes, before a query some ms behind could share it)
+    const bool small = (long long)g->n * Wa < kStepAheadWords;
+    int levels = small || e->nq > kStepQueries ? 1 : e->ahead;
+    while (levels > 1 && bit_length(L + levels - min_base) > w->nplanes) --levels;
+    a.nplanes = std::min(a.nplanes, std::max(bit_length(L + levels - min_base), 1));
+    *e->h_stop = 0;
+    const bool sparse = e->fresh_rows < (u64)g->n / 4;
+    for (int i = 1; i <= levels; ++i) {
+      DAWN_TRY(batch_launch_step_control(a, aw, w->act, L + i, i == 1,
+                                         reinterpret_cast<const u64*>(w->src), e->nq, s));
+      const bool odd = i % 2 == 1;
+      a.vis = e->rows(!odd);
+      DAWN_TRY(batch_launch_step(S->ctx, a, e->rows(odd), L + i, sparse, e->h_stop, s));
+    }
+    e->queued = levels;
+    DAWN_HIP(hipMemcpyAsync(w->h_ctrl, w->ctrl, sizeof(BatchCtrl), hipMemcpyDeviceToHost, s));
+    DAWN_HIP(hipEventRecord(e->lev_ev, s));
+    e->running = true;
+    return DAWN_OK;
+  }
+  // the merge writes only the planes a running lane's level can reach
+  a.nplanes = std::min(a.nplanes, std::max(need, 1));
   DAWN_TRY(batch_launch_level_prep(aw, w->act, w->ctrl, (L + 1) & 1, s));
-  const bool pull = e->have_last ? batch_choose_pull(p, e->last, g->n, Wa) : false;
+  // (after one-pass levels there is no frontier to push)
+  const bool pull = entered || (e->have_last ? batch_choose_pull(p, e->last, g->n, Wa) : false);
   DAWN_TRY(batch_launch_expand(S->ctx, a, pull, L + 1, s));
   DAWN_TRY(batch_launch_merge(S->ctx, a, L + 1, s));
   DAWN_HIP(hipMemcpyAsync(w->h_ctrl, w->ctrl, sizeof(BatchCtrl), hipMemcpyDeviceToHost, s));
@@ -340,10 +419,17 @@ static dawn_status launch_level(Server* S, Engine* e) {
 // The level just finished: retire finished lanes, emit finished queries.
 static dawn_status level_done(Server* S, Engine* e) {
   BatchWs* w = e->ws;
-  e->L += 1;
+  const int ran = e->steps ? w->h_ctrl->run.pull_levels : 1;
+  e->L += ran;
   const int L = e->L;
   e->last = batch_level_sum(w->h_ctrl->lv[L & 1]);
-  e->have_last = true;
+  e->have_last = !e->steps;
+  if (e->steps) {
+    e->buf ^= ran & 1;
+    e->fresh_rows += w->h_ctrl->run.reached + e->last.nodes;
+    // more at a time while they all run
+    e->ahead = ran == e->queued ? std::min(2 * e->ahead, kStepAhead) : ran;
+  }
   std::vector<Query*> done;
   for (int wd = 0; wd < e->W; ++wd) {
     const u64 still = lane_activity(*w->h_ctrl, L & 1, wd);
@@ -374,6 +460,11 @@ static dawn_status level_done(Server* S, Engine* e) {
       break;
     }
   BatchArgs a = batch_args(e->g.get(), w, e->W, We);
+  if (e->steps) {
+    a.fused = 2;
+    a.vis = e->rows(false);
+    a.nxt[0] = e->rows(true);
+  }
   // planes that can hold a bit of a finished lane: its levels reach L - base
   int min_base = L;
   for (Query* q : done) min_base = std::min(min_base, q->base);
@@ -388,6 +479,7 @@ static dawn_status level_done(Server* S, Engine* e) {
       e->owner[lane] = nullptr;
     }
     e->busy_count -= (int)q->lanes.size();
+    e->nq = -1;
     q->emitted = true;
     e->emitting.push_back(q);
   }
@@ -521,7 +613,10 @@ static void scheduler_main(Server* S) {
       }
       if (e->running) {
         const hipError_t le = hipEventQuery(e->lev_ev);
-        if (le == hipErrorNotReady) continue;
+        if (le == hipErrorNotReady) {
+          if (e->queued > 1 && !*e->h_stop && may_admit(S, e)) *e->h_stop = 1;
+          continue;
+        }
         e->running = false;
         dawn_status st = le == hipSuccess
                              ? level_done(S, e)
