@@ -233,6 +233,7 @@ dawn_status dawn_destroy(dawn_ctx* c) {
     ctx->graphs.clear();
   }
   hipDeviceSynchronize();
+  bounces_free(ctx);
   delete ctx;
   return DAWN_OK;
 }

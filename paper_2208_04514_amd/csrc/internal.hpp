@@ -255,6 +255,7 @@ inline size_t sess_cluster_cap(size_t qcap) {
 // ----------------------------------------------------------- host objects --
 struct Ctx;
 struct GraphRec;
+struct Bounce;
 
 // Device memory accounted against the context's budget.  Budget can be set
 // aside with dev_reserve; an allocation `from_reserve` draws on it.
@@ -382,7 +383,17 @@ struct Ctx {
   int32_t next_graph = 0;
   Server* server = nullptr;
   std::mutex server_mu;
+  std::mutex bounce_mu;
+  std::vector<Bounce*> bounces;            // idle pinned buffers (hostcopy.cpp)
+  int bounce_count = 0;                    // idle and taken
 };
+
+// hostcopy.cpp: `rows` rows of n values, one after another on the device, to rows
+// dst_stride values apart on the host, after the stream's work; returns when they
+// are there.
+hipError_t copy_rows_to_host(Ctx* ctx, int32_t* dst, size_t dst_stride, const int32_t* src,
+                             size_t n, size_t rows, hipStream_t s);
+void bounces_free(Ctx* ctx);
 
 dawn_status get_graph(Ctx* ctx, int32_t id, std::shared_ptr<GraphRec>* out);
 dawn_params default_params(const GraphRec& g);

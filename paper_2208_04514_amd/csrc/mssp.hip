@@ -2411,10 +2411,7 @@ dawn_status mssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, const int32_t*
     tot.kernel_ms += group_ms;
   }
   if (st == DAWN_OK && !device_out) {
-    hipError_t e = hipMemcpy2DAsync(dist, (size_t)row_stride * 4, stage, (size_t)g->n * 4,
-                                    (size_t)g->n * 4, (size_t)k, hipMemcpyDeviceToHost,
-                                    ws[0]->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ws[0]->stream);
+    hipError_t e = copy_rows_to_host(ctx, dist, row_stride, stage, g->n, k, ws[0]->stream);
     if (e != hipSuccess) st = fail(DAWN_E_DEVICE, "copy to host: %s", hipGetErrorString(e));
   }
   if (stage) {

@@ -528,8 +528,8 @@ static void copier_main(Server* S) {
     lk.unlock();
     hipError_t he = hipEventSynchronize(q->ev);
     if (he == hipSuccess)
-      he = hipMemcpyAsync(q->out, q->stage, q->stage_bytes, hipMemcpyDeviceToHost, S->copy_stream);
-    if (he == hipSuccess) he = hipStreamSynchronize(S->copy_stream);
+      he = copy_rows_to_host(S->ctx, q->out, q->g->n, q->stage, q->g->n, q->src.size(),
+                             S->copy_stream);
     lk.lock();
     finish_query(S, q, he == hipSuccess ? DAWN_OK : DAWN_E_DEVICE);
   }

@@ -1836,8 +1836,7 @@ dawn_status sssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, int32_t source
   if (rs.done == 2) return fail(DAWN_E_DEVICE, "watchdog: more than n levels");
   if (rs.done != 1) return fail(DAWN_E_DEVICE, "level loop ended without finishing");
   if (!device_out) {
-    DAWN_HIP(hipMemcpyAsync(dist, w->dist, (size_t)g->n * 4, hipMemcpyDeviceToHost, w->stream));
-    DAWN_HIP(hipStreamSynchronize(w->stream));
+    DAWN_HIP(copy_rows_to_host(ctx, dist, g->n, w->dist, g->n, 1, w->stream));
   }
   if (stats) {
     float ms = 0.f;

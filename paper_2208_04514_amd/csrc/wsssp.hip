@@ -710,8 +710,7 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
   else if (w->h_m->end_tag != a.seq || w->h_m->done != 1)
     st = fail(DAWN_E_DEVICE, "weighted level loop did not finish");
   if (st == DAWN_OK && !device_out) {
-    e = hipMemcpyAsync(dist, w->dist, (size_t)g->n * 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    e = copy_rows_to_host(ctx, dist, g->n, w->dist, g->n, 1, s);
     if (e != hipSuccess) st = fail(DAWN_E_DEVICE, "weighted SSSP: %s", hipGetErrorString(e));
   }
   if (st != DAWN_OK) return st;   // the workspace is dropped (its bitmaps may hold bits)
