@@ -29,8 +29,10 @@
 //
 // dawn_mssp and APSP run the level loop on the device: a one-wave control
 // kernel before each level applies the direction rule and ends the run, and
-// the host only enqueues levels in chunks.  Serving steps levels from the
-// host, where it admits and retires queries.
+// the host only enqueues levels in chunks; a narrow batch alone runs them all in
+// one launch (bsession.hip).  Serving steps levels from the host, where it admits
+// and retires queries: expansion and merge as above, or for narrow batches one
+// pass a level (batch_step), a few levels at a time.
 #include <string.h>
 
 #include <algorithm>
@@ -1120,7 +1122,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_step(BatchArgs a, u64* out,
     if (actb[tid] & ~ld_relaxed(gp)) atom_or(gp, actb[tid]);
   }
   if (tid == 0 && fresh) atom_add(&a.ctrl->lv[cl].s[stripe].nodes, (u64)fresh);
-  if (asked) a.ctrl->lv[cl].nchunks = 1;
+  if (asked) a.ctrl->lv[cl].s[0].edges = 1;
 }
 
 // Before one-pass level L.  Several are queued at a time (the round trip to the
@@ -1128,8 +1130,8 @@ __global__ __launch_bounds__(kBatchBlock) void batch_step(BatchArgs a, u64* out,
 // its active lanes from the host, a later one those that found something at the
 // level before.  The rest stand down (run.done) once a query has no active lane
 // left, its rows being due (query i: lanes qmask[i * kStepWords + w]), and when
-// the host asks (a query waits to join; the level before noted it in the slot's
-// nchunks, otherwise unused here).  A level's counters stay in its slot when it
+// the host asks (a query waits to join; the level before noted it in its slot's
+// first edge counter, otherwise unused here).  A level's counters stay in its slot when it
 // was the last.
 __global__ __launch_bounds__(kWave) void batch_step_control(BatchArgs a, BatchActWords act,
                                                            u64* d_act, int L, int first,
@@ -1148,7 +1150,7 @@ __global__ __launch_bounds__(kWave) void batch_step_control(BatchArgs a, BatchAc
   } else {
     if (ld_relaxed(&r->done)) return;
     const int prev = (L - 1) & 1;
-    const unsigned asked = a.ctrl->lv[prev].nchunks;
+    const unsigned asked = (unsigned)a.ctrl->lv[prev].s[0].edges;
     const u64 nodes = wave_sum(lane < kStripes ? a.ctrl->lv[prev].s[lane].nodes : (u64)0);
     u64 still = 0;
     for (int i = 0; i < kStripes; ++i)
@@ -1173,7 +1175,10 @@ __global__ __launch_bounds__(kWave) void batch_step_control(BatchArgs a, BatchAc
   }
   const int cl = L & 1;
   for (int i = lane; i < kStripes * 64; i += kWave) a.ctrl->laneact[cl][i / 64][i % 64] = 0;
-  if (lane < kStripes) a.ctrl->lv[cl].s[lane].nodes = 0;
+  if (lane < kStripes) {
+    a.ctrl->lv[cl].s[lane].nodes = 0;
+    a.ctrl->lv[cl].s[lane].edges = 0;
+  }
   if (lane == 0) a.ctrl->lv[cl].nchunks = 0;
 }
 

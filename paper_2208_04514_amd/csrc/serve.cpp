@@ -384,8 +384,11 @@ static dawn_status launch_level(Server* S, Engine* e) {
     }
     // (one at a time on small rows: a run of a few hundred such levels would be
     // over, 3 ms on 128 x 128 nodes, before a query some ms behind could share it)
-    const bool small = (long long)g->n * Wa < kStepAheadWords;
-    int levels = small || e->nq > kStepQueries ? 1 : e->ahead;
+    // and while other graphs' levels run, which fill the round trip: queued ones
+    // would only hold those up
+    bool alone = (long long)g->n * Wa >= kStepAheadWords && e->nq <= kStepQueries;
+    for (const auto& kv : S->engines) alone = alone && (kv.second == e || !kv.second->running);
+    int levels = alone ? e->ahead : 1;
     while (levels > 1 && bit_length(L + levels - min_base) > w->nplanes) --levels;
     a.nplanes = std::min(a.nplanes, std::max(bit_length(L + levels - min_base), 1));
     *e->h_stop = 0;
