@@ -158,8 +158,8 @@ struct BatchWs {
   int32_t* lane = nullptr;      // lane of each seeded source
   unsigned* flags = nullptr;    // see BatchArgs::flags
   FusedCtrl* fused = nullptr;   // behind flags in the same allocation
-  FusedPart* h_part = nullptr;  // pinned read-back of its totals
-  BatchCtrl* h_ctrl = nullptr;
+  BatchCtrl* h_ctrl = nullptr;  // pinned read-backs: the control block,
+  FusedPart* h_part = nullptr;  //   and behind it a one-launch run's totals
   // the last work enqueued on the workspace (by a call on any stream); whoever
   // takes it next makes its stream wait for this event first
   hipEvent_t busy = nullptr;
