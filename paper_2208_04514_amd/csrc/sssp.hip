@@ -1399,7 +1399,6 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out
 
   // the destructor frees each buffer and returns `bytes` to the budget at once
   if (s != DAWN_OK) return s;
-  DAWN_HIP(hipMemset(w->ctrl, 0, ctrl_bytes + sizeof(SessCtrl)));
   w->sess = reinterpret_cast<SessCtrl*>(reinterpret_cast<char*>(w->ctrl) + ctrl_bytes);
   DAWN_HIP(hipHostMalloc((void**)&w->h_ctrl, sizeof(SsspCtrl), hipHostMallocDefault));
   DAWN_HIP(hipHostMalloc((void**)&w->h_m, sizeof(HostMirror),
@@ -1407,6 +1406,9 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out
   memset(w->h_m, 0, sizeof(HostMirror));
   DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
   DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
+  // on the workspace's stream: hipMemset returns before it has run, in the null
+  // stream, and could clear the block in the middle of the first traversal
+  DAWN_HIP(hipMemsetAsync(w->ctrl, 0, ctrl_bytes + sizeof(SessCtrl), w->stream));
   DAWN_HIP(hipEventCreate(&w->ev0));
   DAWN_HIP(hipEventCreate(&w->ev1));
   *out = std::move(w);

@@ -554,7 +554,6 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
   for (int i = 0; i < 2; ++i) {
     DAWN_TRY(alloc((void**)&w->q[i], (size_t)kSessStripes * sess_queue_cap(g->n, g->m, kWeightPiece) * 8));
     DAWN_TRY(alloc((void**)&w->inq[i], nw * 8 + 64));
-    DAWN_HIP(hipMemset(w->inq[i], 0, nw * 8 + 64));
   }
   DAWN_TRY(alloc((void**)&w->fin, nw * 8));
   DAWN_TRY(alloc((void**)&w->dist, n * 4));
@@ -564,6 +563,8 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
   memset(w->h_m, 0, sizeof(WMirror));
   DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
   DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
+  // on the workspace's stream (hipMemset returns before it has run, in the null stream)
+  for (int i = 0; i < 2; ++i) DAWN_HIP(hipMemsetAsync(w->inq[i], 0, nw * 8 + 64, w->stream));
   DAWN_HIP(hipEventCreateWithFlags(&w->ev1, hipEventDisableTiming));
   *out = std::move(w);
   return DAWN_OK;
