@@ -45,7 +45,11 @@
 // All rounds run in one launch (session_dev.hpp).  A node joins the next
 // frontier once per round: its bit in the next round's membership bitmap is
 // set with an atomic OR, and each round clears the bits of the frontier it
-// consumes, so the bitmap of parity p is clear again when it is next written.
+// consumes, so the bitmap of parity p is clear again when it is next written,
+// but for nodes that dropped without an edge to relax: those are in no queue, and
+// their bits stay until the init kernel of the next run clears both bitmaps.
+// (Within a run nothing is lost by it: such a node drops again only in the same
+// bucket, where it still has no edge to relax.)
 #include <string.h>
 
 #include <algorithm>
@@ -420,14 +424,16 @@ __global__ __launch_bounds__(kSB, 4) void wsssp_session(WArgs a, SessArgs x) {
   session<WeightPolicy>(a, x, sh);
 }
 
-// dist = -1 everywhere but the source, control block clear.
+// dist = -1 everywhere but the source, bitmaps and control block clear.
 __global__ __launch_bounds__(kSB) void wsssp_init(WArgs a, int source) {
   const unsigned tid = blockIdx.x * kSB + threadIdx.x, nt = gridDim.x * kSB;
   if (tid == 0) a.hm->t_start = wall_clock64();
   u64* c = reinterpret_cast<u64*>(a.ctrl);
   for (unsigned i = tid; i < sizeof(WCtrl) / 8; i += nt) c[i] = 0;
-  if (a.split)
-    for (unsigned i = tid; i < (unsigned)a.nw; i += nt) a.fin[i] = 0;
+  for (unsigned i = tid; i < (unsigned)a.nw; i += nt) {
+    a.inq[0][i] = a.inq[1][i] = 0;
+    if (a.split) a.fin[i] = 0;
+  }
   for (unsigned i = tid; i < (unsigned)a.n; i += nt) a.dist[i] = (int)i == source ? 0 : -1;
 }
 
@@ -553,7 +559,7 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
   };
   for (int i = 0; i < 2; ++i) {
     DAWN_TRY(alloc((void**)&w->q[i], (size_t)kSessStripes * sess_queue_cap(g->n, g->m, kWeightPiece) * 8));
-    DAWN_TRY(alloc((void**)&w->inq[i], nw * 8 + 64));
+    DAWN_TRY(alloc((void**)&w->inq[i], nw * 8));
   }
   DAWN_TRY(alloc((void**)&w->fin, nw * 8));
   DAWN_TRY(alloc((void**)&w->dist, n * 4));
@@ -563,8 +569,6 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
   memset(w->h_m, 0, sizeof(WMirror));
   DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
   DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
-  // on the workspace's stream (hipMemset returns before it has run, in the null stream)
-  for (int i = 0; i < 2; ++i) DAWN_HIP(hipMemsetAsync(w->inq[i], 0, nw * 8 + 64, w->stream));
   DAWN_HIP(hipEventCreateWithFlags(&w->ev1, hipEventDisableTiming));
   *out = std::move(w);
   return DAWN_OK;
@@ -714,7 +718,7 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
     e = copy_rows_to_host(ctx, dist, g->n, w->dist, g->n, 1, s);
     if (e != hipSuccess) st = fail(DAWN_E_DEVICE, "weighted SSSP: %s", hipGetErrorString(e));
   }
-  if (st != DAWN_OK) return st;   // the workspace is dropped (its bitmaps may hold bits)
+  if (st != DAWN_OK) return st;   // the workspace is dropped
   const WMirror& m = *w->h_m;
   if (stats) {
     stats->levels = std::max((int32_t)m.rounds, 1);   // rounds that had a frontier
