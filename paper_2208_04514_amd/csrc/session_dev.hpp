@@ -248,6 +248,7 @@ struct SessCount {
   unsigned mf;      // their out-edges (per lane)
   unsigned scan;    // scan levels: the policy's sum (per lane)
   int ahead;        // first target of a row found, loaded ahead of the next level
+  int low;          // for the policy's use (per lane)
 };
 
 // Per-wave counters to the workgroup's.
@@ -453,7 +454,7 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
   unsigned* qn = &slot->q[stripe].n;
   const bool scans = P::scans(sh.p);
   {
-    SessCount c{0, 0, 0, 0};
+    SessCount c{0, 0, 0, 0, 0};
     PieceSink<P, false> sink{sh, qout, qout, sh.own[t / kWave], qn, (unsigned)kStage};
     P::step(a, x, sh, sink, c);
     add_counts(sh, c, scans);
@@ -541,7 +542,7 @@ __device__ __forceinline__ bool cluster_run(const typename P::Args& a, const Ses
     // the counter of the next level was last read before this one began
     if (sh.rank == 0 && t == 0) st_relaxed(&sc->over[(L + 1) % 3].n, 0u);
     {
-      SessCount c{0, 0, 0, 0};
+      SessCount c{0, 0, 0, 0, 0};
       u64* qout = x.q[sh.p.qp ^ 1];
       PieceSink<P, true> sink{sh, qout + (size_t)sh.rank * x.ccap,
                            qout + (size_t)kSessGroup * x.ccap, sh.own[t / kWave],
@@ -620,7 +621,7 @@ __device__ __forceinline__ void solo_run(const typename P::Args& a, const SessAr
   for (;;) {
     u64* nxt = cur == sh.stage ? sh.stage + kSoloCap : sh.stage;
     {
-      SessCount c{0, 0, 0, 0};
+      SessCount c{0, 0, 0, 0, 0};
       ListSink<P> sink{sh, nxt, x.q[sh.p.qp ^ 1]};
       P::solo(a, sh, cur, ncur, sink, c);
       add_counts(sh, c, false);
@@ -689,6 +690,7 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
     if (t < kWave) {
       if (lane == 0) {
         sh.p.step = 0;
+        sh.p.mode = 0;
         sh.p.qp = 0;
         sh.p.stride = x.qcap;
         sh.p.full = 0;

@@ -25,8 +25,10 @@
 // done.  For that the weights come with a copy of the rows whose edges lighter
 // than delta stand first: a round looks at those alone.  The settled nodes have
 // a bitmap, which most targets of the later pass are found in (it stays in the
-// caches; distances at random do not).  An empty bucket doubles the width until
-// a node is found.
+// caches; distances at random do not).  No bucket is empty, however far apart distances
+// lie, so the levels are bounded by the nodes (max_rounds): a collection counts the
+// nodes less than delta past its bucket, and where there is none the next bucket starts
+// at the smallest distance further on, or that the relaxations past T make.
 //
 // delta = kDelta x mean weight / mean out-degree: the denser the graph, the
 // more often an unsettled node's row is relaxed in vain, the sparser, the fewer
@@ -67,8 +69,12 @@ namespace dawn {
 constexpr double kDelta = 16.0;
 constexpr double kDeltaWhole = 32.0;
 // A bucket whose nodes have fewer out-edges than this takes some 25 us whatever
-// it holds: the next is twice as wide.
+// it holds: the next is twice as wide, once half of the graph's edges are settled.
 constexpr unsigned kSmallBucket = 1 << 19;
+// So it is after this many buckets of one workgroup's work in a row: a long path of
+// heavy edges then takes one level a node and not four.  (A path of 2000 edges of
+// weight 100 before a clique: 22 ms without this, 6.1 with; a round a launch 16.)
+constexpr unsigned kThinBuckets = 16;
 
 // What a weighted run leaves for the host (coherent host memory).
 struct WMirror {
@@ -87,6 +93,11 @@ struct WCtrl {
     u64 reached, edges;
   } part[kStripes];
   alignas(kLine) unsigned closed;       // workgroups that have added theirs
+  // kFar - the smallest distance past the bucket that a level came upon (0: none), by
+  // barrier group; three, used in turn
+  struct alignas(kLine) Low {
+    int v;
+  } low[3][kSessGroups];
 };
 
 struct WArgs {
@@ -115,6 +126,7 @@ __device__ __forceinline__ unsigned umin_atomic(int32_t* p, unsigned v) {
 }
 
 constexpr unsigned kUnreached = ~0u;
+constexpr int kFar = 0x7fffffff;        // larger than any distance
 constexpr unsigned kWhole = ~0u;        // piece number of an uncut row
 
 // What a level of the session does.
@@ -134,11 +146,17 @@ struct WeightPolicy {
     unsigned lo, hi;            // the bucket: distances in [lo, hi)
     unsigned width;             // of the next collection
     unsigned rounds;            // near rounds run
-    unsigned beyond;            // reached nodes past the bucket at its collection
+    unsigned far;               // kFar - the next bucket's start (0: none)
+    unsigned gap;               // no node was less than delta past the bucket
+    unsigned lows;              // levels that used WCtrl::low so far
     unsigned settled;           // out-edges of the finished buckets
+    unsigned thin;              // buckets of one workgroup's work in a row
     unsigned steps;
   };
-  using Shared = SessShared<WeightPolicy>;
+  struct Shared : SessShared<WeightPolicy> {
+    int low;                    // this workgroup's part of WCtrl::low
+  };
+  using S = SessShared<WeightPolicy>;
 
   static __device__ __forceinline__ u64 entry(int v, int, int i) {
     return (u64)(unsigned)v | ((u64)(unsigned)i << 32);
@@ -188,6 +206,7 @@ struct WeightPolicy {
           first = !(atom_or(&next[v[0] >> 6], bit) & bit);
           deg = near_degree(a, lite, v[0]);
         }
+        if (!near) c.low = max(c.low, kFar - (int)cand[0]);
       }
       put(first, v[0], deg, sink, c);
     } else {
@@ -195,6 +214,7 @@ struct WeightPolicy {
       for (int i = 0; i < E; ++i) {
         go[i] = false;
         if (has[i] && cand[i] < cur[i]) go[i] = cand[i] < umin_atomic(&a.dist[v[i]], cand[i]);
+        if (go[i] && !near) c.low = max(c.low, kFar - (int)cand[i]);
       }
       if (!near) return;
       bool first[E];
@@ -280,8 +300,9 @@ struct WeightPolicy {
         });
   }
 
-  // One wave per 64 nodes: rows of the nodes in [lo, hi) to the queue, and the
-  // number of reached nodes past it.  settled: they are final.
+  // One wave per 64 nodes: rows of the nodes in [lo, hi) to the queue.  settled: they
+  // are final; else also the number of nodes less than delta past them and the
+  // smallest distance beyond.
   template <class Sink>
   static __device__ __forceinline__ void collect(const WArgs& a, bool settled, bool lite,
                                                  unsigned lo, unsigned hi,
@@ -299,7 +320,12 @@ struct WeightPolicy {
       for (int q = 0; q < 4; ++q) {
         const int v = (int)((w + q * nwaves) * kWave) + lane;
         const bool in = d[q] >= lo && d[q] < hi;
-        if (d[q] >= hi && d[q] != kUnreached) c.scan += 1;
+        if (!settled && d[q] >= hi && d[q] != kUnreached) {
+          if (d[q] - hi < a.delta)
+            c.scan += 1;
+          else
+            c.low = max(c.low, kFar - (int)d[q]);
+        }
         const u64 bits = __ballot(in);
         if (!bits) continue;
         if (settled && lane == 0) {
@@ -312,9 +338,41 @@ struct WeightPolicy {
     }
   }
 
+  // The levels that may have to find the smallest distance past the bucket.
+  static __device__ __forceinline__ bool wants_low(const State& u) {
+    return u.phase == kCollect || (u.phase == kHeavy && u.gap);
+  }
+  static __device__ __forceinline__ void wave_low(S& base, const SessCount& c) {
+    if (__ballot(c.scan != 0)) return;      // not to be asked for
+    const int x = __builtin_amdgcn_readlane(wave_incl_max(c.low), kWave - 1);
+    if (lane_id() == 0 && x) atomicMax(&static_cast<Shared&>(base).low, x);
+  }
+
   template <class Sink>
-  static __device__ __forceinline__ void step(const WArgs& a, const SessArgs& x, Shared& sh,
+  static __device__ __forceinline__ void step(const WArgs& a, const SessArgs& x, S& sh,
                                               Sink& sink, SessCount& c) {
+    level(a, x, sh, sink, c);
+    if (!wants_low(sh.p.u)) return;
+    wave_low(sh, c);
+    __syncthreads();
+    const unsigned k = uniform(sh.p.u.lows);
+    if (threadIdx.x == 0) {
+      Shared& s = static_cast<Shared&>(sh);
+      if (s.low)
+        __hip_atomic_fetch_max(&a.ctrl->low[k % 3][sh.rank / kSessGroup].v, s.low, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+      s.low = 0;
+    }
+    // the next such level's words.  They were last read after the one before last, by
+    // workgroup 0 and the members of its cluster, which have run a level over all
+    // nodes since
+    if (sh.rank == 0 && threadIdx.x < kSessGroups)
+      st_relaxed(&a.ctrl->low[(k + 1) % 3][threadIdx.x].v, 0);
+  }
+
+  template <class Sink>
+  static __device__ __forceinline__ void level(const WArgs& a, const SessArgs& x, S& sh,
+                                               Sink& sink, SessCount& c) {
     const int wv = threadIdx.x / kWave;
     const unsigned K = uniform(sh.p.K);
     const unsigned nwaves = K * kSW;
@@ -333,75 +391,99 @@ struct WeightPolicy {
   }
 
   template <class Sink>
-  static __device__ __forceinline__ void solo(const WArgs& a, Shared& sh, const u64* cur,
+  static __device__ __forceinline__ void solo(const WArgs& a, S& sh, const u64* cur,
                                               unsigned ncur, Sink& sink, SessCount& c) {
     const int wv = threadIdx.x / kWave;
     push<1>(a, sh.own[wv], sh.p.u, (ncur + kWave - 1) / kWave, (unsigned)wv, (unsigned)kSW,
             ListSrc{cur, ncur}, sink, c);
+    if (wants_low(sh.p.u)) wave_low(sh, c);
   }
 
   // What follows the level just run, from the rows it put in the queue (nf, of
-  // mf edges) and, after a collection, the reached nodes past it.
-  static __device__ __forceinline__ void advance(const WArgs& a, Shared& sh, unsigned nf, u64 mf,
-                                                 u64 beyond, bool record) {
+  // mf edges), after a collection the nodes less than delta past it, and the smallest
+  // distance past the bucket where there is none.
+  static __device__ __forceinline__ void advance(const WArgs& a, S& sh, unsigned nf, u64 mf,
+                                                 u64 close, bool record) {
     State u = sh.p.u;
     unsigned done = 0;
     u.steps += 1;
+    unsigned low = 0;
+    if (wants_low(u)) {
+      if (sh.p.mode == kModeSolo) {
+        low = (unsigned)static_cast<Shared&>(sh).low;
+      } else {
+        if (!close) {
+          const int g = lane_id() & (kSessGroups - 1);
+          low = (unsigned)__builtin_amdgcn_readlane(
+              wave_incl_max(ld_relaxed(&a.ctrl->low[u.lows % 3][g].v)), kWave - 1);
+        }
+        u.lows += 1;
+      }
+    }
     switch (u.phase) {
       case kNear:
         u.rounds += 1;
         u.par ^= 1;
         if (nf) break;
-        if (a.split)
+        if (a.split) {
           u.phase = kSettled;
-        else
-          next_bucket(u, a.delta);
+        } else {
+          // (no edge is longer than the bucket: the next holds a node, or none is left)
+          u.far = (unsigned)kFar - u.hi;
+          done = next_bucket(u, a.delta);
+        }
         break;
       case kSettled:
         // (nobody with an edge: what lies past the bucket is as it was)
         if (nf)
           u.phase = kHeavy;
-        else if (u.beyond)
-          next_bucket(u, min(u.width * 2, 1u << 30));
         else
-          done = 1;
+          done = next_bucket(u, u.width);
         break;
       case kHeavy:
-        // past the bulk of the edges, buckets of little work: fewer, wider ones
+        // (with a gap, the smallest of what lay past it before and what this level made)
+        u.far = max(u.far, low);
+        // past the bulk of the edges, and on long stretches of next to none, buckets
+        // of little work: fewer, wider ones
         u.settled += sh.p.fe;
-        next_bucket(u, sh.p.fe < kSmallBucket && u.settled > a.half ? min(u.width * 2, 1u << 30)
-                                                                    : a.delta);
+        u.thin = sh.p.fe <= (unsigned)kSoloCap ? u.thin + 1 : 0;
+        done = next_bucket(u, (sh.p.fe < kSmallBucket && u.settled > a.half) || u.thin > kThinBuckets
+                                  ? min(u.width * 2, 1u << 30)
+                                  : a.delta);
         break;
       default:
-        u.beyond = (unsigned)beyond;
+        u.gap = close == 0;
+        u.far = close ? (unsigned)kFar - u.hi : low;
         if (nf)
           u.phase = kNear;
         else if (a.split)
-          u.phase = kSettled;
-        else if (beyond)
-          next_bucket(u, min(u.width * 2, 1u << 30));
+          u.phase = kSettled;       // its nodes have heavy edges, or none
         else
-          done = 1;
+          done = next_bucket(u, u.width);
     }
     if (u.steps > a.max_rounds) done = 2;
     set_plan<WeightPolicy>(sh, done != 0, u.phase == kSettled || u.phase == kCollect, mf, a.nw,
                            kSoloCap);
     if (lane_id() == 0) {
       sh.p.u = u;
+      static_cast<Shared&>(sh).low = 0;
       if (done && record) {
         a.ctrl->done = done;
         a.ctrl->rounds = u.rounds;
       }
     }
   }
-  static __device__ __forceinline__ void next_bucket(State& u, unsigned width) {
+  // The bucket that starts at the smallest distance left; 1 if there is none.
+  static __device__ __forceinline__ unsigned next_bucket(State& u, unsigned width) {
+    if (!u.far) return 1;
     u.phase = kCollect;
-    u.lo = u.hi;
+    u.lo = (unsigned)kFar - u.far;
     u.width = width;
-    u.hi = min(u.lo + width, 0x7fffffffu);
+    u.hi = min(u.lo + width, (unsigned)kFar);
+    return 0;
   }
 
-  static __device__ __forceinline__ void begin(const WArgs& a, const SessArgs& x, Shared& sh) {
+  static __device__ __forceinline__ void begin(const WArgs& a, const SessArgs& x, S& sh) {
     const int s = x.source;
     const int deg = near_degree(a, a.light != nullptr, s);
     if (lane_id() == 0) {
@@ -410,7 +492,7 @@ struct WeightPolicy {
       u.par = 0;
       u.lo = 0;
       u.hi = u.width = a.delta;
-      u.rounds = u.steps = u.beyond = u.settled = 0;
+      u.rounds = u.steps = u.far = u.gap = u.lows = u.settled = u.thin = 0;
       sh.stage[0] = row_entry(s, deg);
       st_relaxed64(&x.q[0][0], row_entry(s, deg));
     }
@@ -420,7 +502,8 @@ struct WeightPolicy {
 };
 
 __global__ __launch_bounds__(kSB, 4) void wsssp_session(WArgs a, SessArgs x) {
-  __shared__ SessShared<WeightPolicy> sh;
+  __shared__ WeightPolicy::Shared sh;
+  if (threadIdx.x == 0) sh.low = 0;
   session<WeightPolicy>(a, x, sh);
 }
 
@@ -680,9 +763,13 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
       a.light = g->w_light;
     }
   }
-  // a near round but a bucket's last settles a node, and a bucket takes at most
-  // four levels more
-  a.max_rounds = (unsigned)std::min<long long>(6ll * g->n + 256, 0xffffffffll);
+  // Every bucket but an empty last one holds a reached node that no earlier one held
+  // (distances past a bucket are lowered to no less than its end), so there are at most
+  // n + 1.  After
+  // r near rounds the nodes are exact whose shortest paths have at most r edges
+  // within the bucket, so a bucket of b nodes takes at most b; its collection, that of
+  // its settled nodes and the relaxations past it are three levels more.
+  a.max_rounds = (unsigned)std::min<long long>(4ll * g->n + 4, 0xffffffffll);
   SessArgs x;
   x.sc = &w->ctrl->sess;
   x.q[0] = w->q[0];
