@@ -592,12 +592,16 @@ __device__ __forceinline__ bool cluster_run(const typename P::Args& a, const Ses
         set_segments(sh, seg);
         P::advance(a, sh, (unsigned)nf, mf, sum, sh.rank == 0);
         if (lane == 0) {
-          sh.nf = sh.mf = sh.scan = sh.n_out = 0;
           sh.p.qp ^= 1;
           sh.p.stride = x.ccap;
         }
       }
-      if (lane == 0) sh.ok = state;
+      // (state 2 too: the counters are the reported level's, and the workgroup goes on
+      // to a level of the later run)
+      if (lane == 0) {
+        sh.nf = sh.mf = sh.scan = sh.n_out = 0;
+        sh.ok = state;
+      }
     }
     __syncthreads();
     if (sh.ok != 1) return sh.ok == 2;

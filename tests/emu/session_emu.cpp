@@ -1,0 +1,222 @@
+// The session frame and its two single-source policies on the host, under random
+// schedules: session_emu KIND SEED0 SEEDS [grid=N hold=P held=N late=P ...].
+// Prints one line and exits nonzero at the first run whose distances or totals
+// differ from a plain search's.
+#include <hip/hip_runtime.h>
+
+#include <stdio.h>
+
+#include <queue>
+#include <random>
+
+#include "session.hip"
+#include "wsssp.hip"
+
+#include "emu.hpp"
+
+namespace dawn {
+dawn_status fail(dawn_status st, const char*, ...) { return st; }
+void clear_error() {}
+dawn_status dev_alloc(Ctx*, void**, size_t, bool) { return DAWN_E_NO_MEMORY; }
+void dev_free(Ctx*, void*, size_t) {}
+hipError_t copy_rows_to_host(Ctx*, int32_t*, size_t, const int32_t*, size_t, size_t, hipStream_t) {
+  return hipSuccess;
+}
+}  // namespace dawn
+using namespace dawn;
+
+struct Graph {
+  int n = 0;
+  std::vector<int> rp, col, ip, isrc, wt;
+  std::vector<u64> noin;
+};
+
+// Stretches of one node a level, fans of up to `wide` nodes, random edges between
+// near levels: frontiers of one edge up to a few hundred, in no order.
+static Graph make(std::mt19937_64& g, int levels, int wide, int wmax) {
+  std::vector<std::vector<int>> at(levels);
+  int n = 0;
+  int width = 1;
+  for (int l = 0; l < levels; ++l) {
+    if (g() % 5 == 0) width = 1 + (int)(g() % (unsigned)wide);
+    else if (g() % 3 == 0) width = 1;
+    for (int i = 0; i < width; ++i) at[l].push_back(n++);
+  }
+  n += 3;                                  // and some no path leads to
+  std::vector<std::pair<int, int>> e;
+  for (int l = 1; l < levels; ++l)
+    for (int v : at[l]) {
+      e.push_back({at[l - 1][g() % at[l - 1].size()], v});
+      for (int k = (int)(g() % 4); k > 0; --k) {
+        const int a = std::max(0, l - 1 - (int)(g() % 3));
+        e.push_back({at[a][g() % at[a].size()], v});
+        if (g() % 2) e.push_back({v, at[a][g() % at[a].size()]});
+      }
+    }
+  std::sort(e.begin(), e.end());
+  Graph r;
+  r.n = n;
+  r.rp.assign(n + 1, 0);
+  r.ip.assign(n + 1, 0);
+  for (auto& x : e) ++r.rp[x.first + 1], ++r.ip[x.second + 1];
+  for (int i = 0; i < n; ++i) r.rp[i + 1] += r.rp[i], r.ip[i + 1] += r.ip[i];
+  r.isrc.resize(e.size() + 1);
+  std::vector<int> pos(r.ip.begin(), r.ip.end() - 1);
+  for (auto& x : e) {
+    r.col.push_back(x.second);
+    r.wt.push_back(g() % 8 ? (int)(g() % 3) : (int)(g() % (unsigned)wmax));
+    r.isrc[pos[x.second]++] = x.first;
+  }
+  r.col.push_back(0);
+  r.wt.push_back(0);
+  r.noin.assign((n + 63) / 64, 0);
+  for (int v = 0; v < n; ++v)
+    if (r.ip[v] == r.ip[v + 1]) r.noin[v / 64] |= 1ull << (v % 64);
+  return r;
+}
+
+static std::vector<int> search(const Graph& g, int s, bool weighted) {
+  std::vector<int> d(g.n, -1);
+  std::priority_queue<std::pair<int, int>> q;
+  q.push({0, s});
+  while (!q.empty()) {
+    const int du = -q.top().first, u = q.top().second;
+    q.pop();
+    if (d[u] >= 0) continue;
+    d[u] = du;
+    for (int i = g.rp[u]; i < g.rp[u + 1]; ++i)
+      if (d[g.col[i]] < 0) q.push({-(du + (weighted ? g.wt[i] : 1)), g.col[i]});
+  }
+  return d;
+}
+
+struct Queues {
+  std::vector<u64> q[2];
+  SessArgs x{};
+  Queues(const Graph& g, int piece, SessCtrl* sc, int s) {
+    x.qcap = (unsigned)sess_queue_cap(g.n, (long long)g.col.size() - 1, piece);
+    x.ccap = (unsigned)sess_cluster_cap(x.qcap);
+    x.sc = sc;
+    x.source = s;
+    for (int i = 0; i < 2; ++i) {
+      q[i].assign((size_t)kSessStripes * x.qcap, ~0ull - 5);     // (no entry stands for a row)
+      x.q[i] = q[i].data();
+    }
+  }
+};
+
+static int failed(const char* what, unsigned long long seed) {
+  printf("seed %llu: %s\n", seed, what);
+  return 1;
+}
+
+int main(int argc, char** argv) {
+  const std::string kind = argv[1];
+  const unsigned long long seed0 = strtoull(argv[2], nullptr, 10);
+  const int seeds = atoi(argv[3]);
+  std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},
+                                  {"levels", 60}, {"wide", 120}, {"small", 6}, {"wmax", 40},
+                                  {"ticks", 0.02}, {"mode", 3}};
+  for (int i = 4; i < argc; ++i) {
+    const std::string a = argv[i];
+    const size_t eq = a.find('=');
+    if (eq == a.npos || !o.count(a.substr(0, eq))) return failed("option", 0);
+    o[a.substr(0, eq)] = atof(a.c_str() + eq + 1);
+  }
+  unsigned long long most = 0;
+  for (unsigned long long seed = seed0; seed < seed0 + seeds; ++seed) {
+    std::mt19937_64 rnd(seed);
+    const Graph g = make(rnd, (int)o["levels"], (int)o["wide"], (int)o["wmax"]);
+    const int m = (int)g.col.size() - 1, s = 0;
+    const bool weighted = kind == "weighted";
+    const std::vector<int> want = search(g, s, weighted);
+    long long reached = 0, edges = 0;
+    for (int v = 0; v < g.n; ++v)
+      if (want[v] >= 0) ++reached, edges += g.rp[v + 1] - g.rp[v];
+
+    emu::Launch l;
+    l.grid = (unsigned)o["grid"];
+    l.block = kSB;
+    l.seed = seed;
+    l.hold = o["hold"];
+    l.held_for = (unsigned)o["held"];
+    l.ticks = o["ticks"];
+    const double late = o["late"];
+    std::vector<unsigned long long> start(l.grid, 0);
+    for (unsigned b = 1; b < l.grid; ++b)
+      if ((double)(rnd() % 1000) < late * 1000) start[b] = rnd() % 400000;
+    l.start = [&](unsigned b) { return start[b]; };
+
+    std::vector<int> dist(g.n, -1);
+    dist[s] = 0;
+    const int nw = (g.n + 63) / 64;
+    if (!weighted) {
+      std::unique_ptr<SsspCtrl> ctrl(new SsspCtrl());
+      std::unique_ptr<SessCtrl> sc(new SessCtrl());
+      memset((void*)ctrl.get(), 0, sizeof(SsspCtrl));
+      memset((void*)sc.get(), 0, sizeof(SessCtrl));
+      std::vector<u64> vis0(nw, 0), vis1(nw, 0);
+      vis0[0] = 1;
+      std::vector<int> level_nf(g.n + 1);
+      std::vector<uint8_t> dir(g.n + 1);
+      SsspArgs a;
+      memset(&a, 0, sizeof(a));
+      a.n = g.n, a.nw = nw, a.m = m;
+      a.rp = g.rp.data(), a.col = g.col.data(), a.ip = g.ip.data(), a.isrc = g.isrc.data();
+      a.noin = g.noin.data(), a.vis0 = vis0.data(), a.vis1 = vis1.data();
+      a.ctrl = ctrl.get(), a.dist = dist.data();
+      a.mode = (int)o["mode"], a.alpha = 14, a.beta = 24, a.lane_edges = 4;
+      a.small_edges = (int)o["small"];
+      a.level_nf = level_nf.data(), a.level_dir = dir.data(), a.lrec = g.n + 1;
+      Queues q(g, kHopPiece, sc.get(), s);
+      std::vector<std::unique_ptr<HopPolicy::Shared>> sh(l.grid);
+      for (auto& p : sh) p.reset(new HopPolicy::Shared());
+      const unsigned long long used =
+          emu::run(l, [&](unsigned b) { session<HopPolicy>(a, q.x, *sh[b]); });
+      if (!used) return failed("no end", seed);
+      most = std::max(most, used);
+      const LevelState& st = ctrl->st[1];
+      if (st.done != 1) return failed("not done", seed);
+      if (st.reached != (u64)reached || st.source_edges != (u64)edges) return failed("totals", seed);
+    } else {
+      std::unique_ptr<WCtrl> ctrl(new WCtrl());
+      memset((void*)ctrl.get(), 0, sizeof(WCtrl));
+      std::vector<u64> fin(nw, 0), in0(nw, 0), in1(nw, 0);
+      WArgs a;
+      memset(&a, 0, sizeof(a));
+      a.n = g.n, a.nw = nw, a.rp = g.rp.data();
+      a.col = g.col.data(), a.wt = g.wt.data(), a.dist = dist.data();
+      a.fin = fin.data(), a.inq[0] = in0.data(), a.inq[1] = in1.data(), a.ctrl = ctrl.get();
+      int mx = 0;
+      for (int w : g.wt) mx = std::max(mx, w);
+      a.delta = 1 + (unsigned)(rnd() % 12);
+      a.split = (int)a.delta < mx;
+      std::vector<int> scol(g.col), swt(g.wt), light(g.n, 0);
+      if (a.split && seed % 2) {                        // rows with the light edges first
+        for (int v = 0; v < g.n; ++v) {
+          std::vector<std::pair<int, int>> r;
+          for (int i = g.rp[v]; i < g.rp[v + 1]; ++i) r.push_back({g.wt[i], g.col[i]});
+          std::stable_partition(r.begin(), r.end(), [&](auto& x) { return x.first < (int)a.delta; });
+          for (size_t i = 0; i < r.size(); ++i) {
+            swt[g.rp[v] + i] = r[i].first, scol[g.rp[v] + i] = r[i].second;
+            light[v] += r[i].first < (int)a.delta;
+          }
+        }
+        a.col = scol.data(), a.wt = swt.data(), a.light = light.data();
+      }
+      a.half = (unsigned)(m / 2);
+      a.max_rounds = (unsigned)(4 * g.n + 4);
+      Queues q(g, kWeightPiece, &ctrl->sess, s);
+      std::vector<std::unique_ptr<WeightPolicy::Shared>> sh(l.grid);
+      for (auto& p : sh) p.reset(new WeightPolicy::Shared()), p->low = 0;
+      const unsigned long long used =
+          emu::run(l, [&](unsigned b) { session<WeightPolicy>(a, q.x, *sh[b]); });
+      if (!used) return failed("no end", seed);
+      most = std::max(most, used);
+      if (ctrl->done != 1) return failed(ctrl->done == 2 ? "too many levels" : "not done", seed);
+    }
+    if (dist != want) return failed("distances", seed);
+  }
+  printf("%d runs, at most %llu picks\n", seeds, most);
+  return 0;
+}
