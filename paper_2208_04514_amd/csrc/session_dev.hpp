@@ -48,7 +48,8 @@
 // atomic when it starts; workgroup 0 closes the list when the first level
 // that needs others comes up; whoever starts later leaves at once.  Every
 // wait is on workgroups that have joined, hence on running ones, and is
-// bounded besides.
+// bounded besides.  The bound is on a wait for the next record, so a long run of
+// solo or cluster levels publishes one now and then.
 #pragma once
 
 #include <algorithm>
@@ -73,6 +74,9 @@ constexpr int kClusterWords = 1024;
 // Grid push: frontier edges per workgroup taking part (half a step of 64 a wave).
 constexpr int kEdgesPerWg = 256;
 constexpr u64 kClosed = 1ull << 63;
+// Solo or cluster levels between two records at most: some 15 ms, against the 10 s
+// that workgroups without work wait for one.
+constexpr unsigned kRecordLevels = 4096;
 
 enum SessMode { kModeGrid = 1, kModeCluster = 2, kModeSolo = 3, kModeEnd = 4 };
 
@@ -530,12 +534,14 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
 // level's sums and takes the same decision.  A member cannot be two levels
 // ahead of another, so two lines do.  On return sh holds the next level's
 // plan, which only workgroup 0 uses; the others take it from the next record.
-// Returns false if a wait timed out.
+// After kRecordLevels levels all leave, whatever the next is.  Returns false if a
+// wait timed out.
 template <class P>
 __device__ __forceinline__ bool cluster_run(const typename P::Args& a, const SessArgs& x,
                                             SessShared<P>& sh) {
   const int t = threadIdx.x, lane = lane_id();
   SessCtrl* sc = x.sc;
+  const unsigned first = uniform(sh.p.step);
   for (;;) {
     const unsigned L = uniform(sh.p.step);
     const bool scans = P::scans(sh.p);
@@ -605,7 +611,7 @@ __device__ __forceinline__ bool cluster_run(const typename P::Args& a, const Ses
     }
     __syncthreads();
     if (sh.ok != 1) return sh.ok == 2;
-    if (sh.p.mode != kModeCluster) {
+    if (sh.p.mode != kModeCluster || L - first >= kRecordLevels - 1) {
       // clear for the next run, which starts with a record of workgroup 0
       // after its next wait for its stores
       if (sh.rank == 0 && t < 3) st_relaxed(&sc->over[t].n, 0u);
@@ -615,14 +621,15 @@ __device__ __forceinline__ bool cluster_run(const typename P::Args& a, const Ses
 }
 
 // ---------------------------------------------------------------- solo levels --
-// Workgroup 0 alone.  On entry `cur` holds ncur rows and sh.p the level to run;
-// on return sh.p is the next level, its queue written, or the end.
+// Workgroup 0 alone, up to kRecordLevels levels.  On entry `cur` holds ncur rows and
+// sh.p the level to run; on return sh.p is the next level, its queue written, or the
+// end.
 template <class P>
 __device__ __forceinline__ void solo_run(const typename P::Args& a, const SessArgs& x,
                                          SessShared<P>& sh, u64* cur, unsigned ncur) {
   const int t = threadIdx.x, wv = t / kWave, lane = lane_id();
   int ahead = 0;
-  for (;;) {
+  for (unsigned ran = 1;; ++ran) {
     u64* nxt = cur == sh.stage ? sh.stage + kSoloCap : sh.stage;
     {
       SessCount c{0, 0, 0, 0, 0};
@@ -645,7 +652,7 @@ __device__ __forceinline__ void solo_run(const typename P::Args& a, const SessAr
       const unsigned nf = uniform(sh.nf), mf = uniform(sh.mf);
       P::advance(a, sh, nf, mf, 0ull, true);
       wave_sync();
-      const bool solo = sh.p.mode == kModeSolo;
+      const bool solo = sh.p.mode == kModeSolo && ran < kRecordLevels;
       if (!solo) set_segments(sh, lane == 0 ? ncur : 0u);
       if (lane == 0) {
         sh.nf = sh.mf = 0;
@@ -720,7 +727,7 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
     if (lead) {
       // close the member list the first time, then publish the plan
       if (t < kWave) {
-        if (sh.p.mode != kModeEnd && !ranked) {
+        if (sh.p.mode != kModeEnd && sh.p.mode != kModeSolo && !ranked) {
           bool full = sh.p.full != 0;
           while (!full) {
             const u64 w = lane < kSessGroups ? ld_relaxed(&sc->joined[lane].w) : 0ull;
@@ -748,13 +755,13 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
         }
         sess_publish(sc, sh, gen + 1);
       }
-      ranked = ranked || sh.p.mode != kModeEnd;
+      ranked = ranked || (sh.p.mode != kModeEnd && sh.p.mode != kModeSolo);
       gen += 1;
       lead = false;
       __syncthreads();
     }
     if (sh.p.mode == kModeEnd) return;
-    if (!ranked) {
+    if (!ranked && sh.p.mode != kModeSolo) {
       if (!sh.p.full) {
         __syncthreads();
         if (t < kWave)

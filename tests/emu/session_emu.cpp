@@ -32,13 +32,14 @@ struct Graph {
 };
 
 // Stretches of one node a level, fans of up to `wide` nodes, random edges between
-// near levels: frontiers of one edge up to a few hundred, in no order.
-static Graph make(std::mt19937_64& g, int levels, int wide, int wmax) {
+// near levels: frontiers of one edge up to a few hundred, in no order; first a path.
+static Graph make(std::mt19937_64& g, int levels, int wide, int wmax, int path) {
   std::vector<std::vector<int>> at(levels);
   int n = 0;
   int width = 1;
   for (int l = 0; l < levels; ++l) {
-    if (g() % 5 == 0) width = 1 + (int)(g() % (unsigned)wide);
+    if (l < path) width = 1;
+    else if (g() % 5 == 0) width = 1 + (int)(g() % (unsigned)wide);
     else if (g() % 3 == 0) width = 1;
     for (int i = 0; i < width; ++i) at[l].push_back(n++);
   }
@@ -116,7 +117,7 @@ int main(int argc, char** argv) {
   const int seeds = atoi(argv[3]);
   std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},
                                   {"levels", 60}, {"wide", 120}, {"small", 6}, {"wmax", 40},
-                                  {"ticks", 0.02}, {"mode", 3}};
+                                  {"ticks", 0.02}, {"mode", 3}, {"path", 0}};
   for (int i = 4; i < argc; ++i) {
     const std::string a = argv[i];
     const size_t eq = a.find('=');
@@ -126,7 +127,8 @@ int main(int argc, char** argv) {
   unsigned long long most = 0;
   for (unsigned long long seed = seed0; seed < seed0 + seeds; ++seed) {
     std::mt19937_64 rnd(seed);
-    const Graph g = make(rnd, (int)o["levels"], (int)o["wide"], (int)o["wmax"]);
+    const Graph g = make(rnd, (int)o["levels"], (int)o["wide"], (int)o["wmax"],
+                         (int)o["path"]);
     const int m = (int)g.col.size() - 1, s = 0;
     const bool weighted = kind == "weighted";
     const std::vector<int> want = search(g, s, weighted);

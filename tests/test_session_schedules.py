@@ -15,6 +15,7 @@ CSRC = os.path.join(ROOT, "paper_2208_04514_amd", "csrc")
 EMU = os.path.join(ROOT, "tests", "emu")
 SMALL = {"kSB = 512;": "kSB = 128;", "kClusterEdges = 32768;": "kClusterEdges = 150;",
          "kEdgesPerWg = 256;": "kEdgesPerWg = 8;", "kClusterWords = 1024;": "kClusterWords = 6;"}
+RECORDS = ("constexpr unsigned kRecordLevels = 4096;", "constexpr unsigned kRecordLevels = 8;")
 
 
 @pytest.fixture(scope="module")
@@ -25,9 +26,9 @@ def emu(tmp_path_factory):
     path = os.path.join(d, "session_dev.hpp")
     with open(path) as f:
         text = f.read()
-    for a, b in SMALL.items():
-        assert text.count("constexpr int " + a) == 1, a
-        text = text.replace("constexpr int " + a, "constexpr int " + b)
+    for a, b in [("constexpr int " + x, "constexpr int " + y) for x, y in SMALL.items()] + [RECORDS]:
+        assert text.count(a) == 1, a
+        text = text.replace(a, b)
     with open(path, "w") as f:
         f.write(text)
     exe = os.path.join(d, "session_emu")
@@ -60,3 +61,10 @@ def test_member_overtaken(emu):
     emu("hop", 200003, 1, jobs=1, grid=34, hold=0.001, held=20000, levels=50, wide=40)
     emu("hop", 1, 16, grid=34, hold=0.001, held=20000, levels=50, wide=40)
     emu("weighted", 1, 8, grid=34, hold=0.001, held=20000, levels=40, wide=40)
+
+
+@pytest.mark.parametrize("kind,small", [("hop", 40), ("hop", 0), ("weighted", 6)])
+def test_long_path_before_wide_levels(emu, kind, small):
+    """Levels of one workgroup, or of one cluster, for several times the wait that
+    workgroups without work are given, then levels that need them."""
+    emu(kind, 1, 4, grid=40, ticks=6000, path=300, levels=320, small=small, wide=400, wmax=3)
