@@ -428,8 +428,13 @@ struct BatchPolicy {
     if (lane_id() == 0) sh.p.u = u;
     wave_sync();
     set_plan<BatchPolicy>(sh, done != 0, true, 0ull, words(a), 0);
-    if (lane_id() == 0 && done) {
-      if (done != 1) leave(a, u, done);
+    if (lane_id() == 0 && done != 1) {
+      // (a run that goes on after a stop for planes still says so: one that ends without
+      // a word of its own must not be taken for stopped again)
+      if (done)
+        leave(a, u, done);
+      else
+        r->done = 0;
     }
   }
 };

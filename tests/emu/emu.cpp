@@ -141,7 +141,12 @@ unsigned long long wave_op(Op op, unsigned long long x, int arg, int rows) {
 }
 void block_sync() { yield(kAtBlock); }
 void pause() { yield(kPaused); }
-unsigned long long clock() { return (unsigned long long)((double)picks * cfg.ticks); }
+unsigned long long clock() {
+  double t = (double)picks;
+  if (cfg.stalled >= 0 && picks > cfg.stall_from)
+    t += (double)(picks - cfg.stall_from) * 1e5;
+  return (unsigned long long)(t * cfg.ticks);
+}
 
 unsigned long long run(const Launch& l, const std::function<void(unsigned)>& kernel) {
   cfg = l;
@@ -183,6 +188,7 @@ unsigned long long run(const Launch& l, const std::function<void(unsigned)>& ker
     const unsigned i = live[at];
     Wave& w = waves[i];
     if (picks < w.asleep || all(w, kAtBlock)) continue;
+    if ((int)w.block == l.stalled && picks >= l.stall_from && picks < l.stall_to) continue;
     if (l.hold > 0 && (double)(draw() >> 11) / 9007199254740992.0 < l.hold)
       w.asleep = picks + l.held_for;
     for (int j = 63; j >= 0; --j)

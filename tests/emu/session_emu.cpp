@@ -1,5 +1,5 @@
-// The session frame and its two single-source policies on the host, under random
-// schedules: session_emu KIND SEED0 SEEDS [grid=N hold=P held=N late=P ...].
+// The session frame and its policies on the host, under random schedules:
+// session_emu hop|weighted|batch SEED0 SEEDS [grid=N hold=P held=N late=P ...].
 // Prints one line and exits nonzero at the first run whose distances or totals
 // differ from a plain search's.
 #include <hip/hip_runtime.h>
@@ -9,6 +9,7 @@
 #include <queue>
 #include <random>
 
+#include "bsession.hip"
 #include "session.hip"
 #include "wsssp.hip"
 
@@ -111,13 +112,85 @@ static int failed(const char* what, unsigned long long seed) {
   return 1;
 }
 
+// A narrow batch of k sources on P words, its level planes growing by one from run to
+// run.  stall: the second run's barrier is made to time out, and that run has to
+// be told from one that wants more planes (it has enough of them).
+template <int P>
+static const char* batch(const Graph& g, int k, emu::Launch l, bool stall) {
+  const int nw = (g.n + 63) / 64;
+  std::unique_ptr<BatchCtrl> ctrl(new BatchCtrl());
+  std::unique_ptr<FusedCtrl> fc(new FusedCtrl());
+  memset((void*)ctrl.get(), 0, sizeof(BatchCtrl));
+  memset((void*)fc.get(), 0, sizeof(FusedCtrl));
+  std::vector<u64> vis((size_t)g.n * P, 0), nxt(vis), t0(nw, 0), t1(nw, 0);
+  std::vector<std::vector<u64>> planes;
+  unsigned flags[2] = {1, 0};
+  std::vector<int> pcv, pck;
+  for (int v = 0; v < g.n; ++v)
+    if (g.ip[v + 1] - g.ip[v] >= kPullBig)
+      for (int i = 0; i * kPullChunk < g.ip[v + 1] - g.ip[v]; ++i) pcv.push_back(v), pck.push_back(i);
+  BsArgs a;
+  memset((void*)&a, 0, sizeof(a));
+  a.fc = fc.get();
+  BatchArgs& b = a.b;
+  b.n = g.n, b.W = b.Ws = (k + 63) / 64, b.m = (long long)g.col.size() - 1;
+  b.rp = g.rp.data(), b.col = g.col.data(), b.ip = g.ip.data(), b.isrc = g.isrc.data();
+  b.pcv = pcv.data(), b.pck = pck.data(), b.npc = (int)pcv.size();
+  b.vis = vis.data(), b.nxt[0] = nxt.data();
+  b.touched[0] = t0.data(), b.touched[1] = t1.data();
+  b.ctrl = ctrl.get(), b.flags = flags, b.wide_scan = 8;
+  std::vector<int> src(k);
+  for (int i = 0; i < k; ++i) {
+    const int s = src[i] = i == 0 ? 0 : (int)((unsigned)i * 2654435761u % (unsigned)g.n);
+    vis[(size_t)s * b.Ws + i / 64] |= 1ull << (i % 64);
+    if (!((t0[s / 64] >> (s % 64)) & 1)) ++fc->touched;
+    t0[s / 64] |= 1ull << (s % 64);
+    fc->lact[0][0].w[i / 64] |= 1ull << (i % 64);
+    ++fc->part[0].reached;
+  }
+  fc->level = 1;
+  SessArgs x;
+  memset((void*)&x, 0, sizeof(x));
+  x.sc = &fc->sess;
+  for (int run = 0;; ++run) {
+    for (int i = 0; i < (stall && run == 1 ? 4 : 1); ++i) planes.emplace_back(vis.size(), 0ull);
+    b.nplanes = (int)planes.size();
+    for (int i = 0; i < b.nplanes; ++i) b.planes[i] = planes[i].data();
+    if (run) memset((void*)&fc->sess, 0, sizeof(SessCtrl));
+    l.stalled = stall && run == 1 ? (int)l.grid / 2 : -1;
+    std::vector<std::unique_ptr<typename BatchPolicy<P>::Shared>> sh(l.grid);
+    for (auto& p : sh) p.reset(new typename BatchPolicy<P>::Shared()), p->edges = p->reached = p->degs = 0;
+    if (!emu::run(l, [&](unsigned w) { session<BatchPolicy<P>>(a, x, *sh[w]); })) return "no end";
+    for (auto& p : sh) fc->part[0].reached += p->reached;
+    if (l.stalled >= 0) return ctrl->run.done == 0 ? nullptr : "a run that timed out says otherwise";
+    if (ctrl->run.done != 4) break;
+  }
+  if (ctrl->run.done != 1) return "not done";
+  const std::vector<u64>& rows = ctrl->run.vis_buf ? nxt : vis;
+  u64 reached = 0;
+  for (int i = 0; i < k; ++i) {
+    const std::vector<int> want = search(g, src[i], false);
+    for (int v = 0; v < g.n; ++v) {
+      const size_t at = (size_t)v * b.Ws + i / 64;
+      int d = -1;
+      if ((rows[at] >> (i % 64)) & 1) {
+        d = 0;
+        for (int p = 0; p < b.nplanes; ++p) d |= (int)((planes[p][at] >> (i % 64)) & 1) << p;
+        ++reached;
+      }
+      if (d != want[v]) return "distances";
+    }
+  }
+  return reached == fc->part[0].reached ? nullptr : "totals";
+}
+
 int main(int argc, char** argv) {
   const std::string kind = argv[1];
   const unsigned long long seed0 = strtoull(argv[2], nullptr, 10);
   const int seeds = atoi(argv[3]);
   std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},
                                   {"levels", 60}, {"wide", 120}, {"small", 6}, {"wmax", 40},
-                                  {"ticks", 0.02}, {"mode", 3}, {"path", 0}};
+                                  {"ticks", 0.02}, {"mode", 3}, {"path", 0}, {"k", 40}, {"stall", 0}};
   for (int i = 4; i < argc; ++i) {
     const std::string a = argv[i];
     const size_t eq = a.find('=');
@@ -149,6 +222,14 @@ int main(int argc, char** argv) {
       if ((double)(rnd() % 1000) < late * 1000) start[b] = rnd() % 400000;
     l.start = [&](unsigned b) { return start[b]; };
 
+    if (kind == "batch") {
+      const int k = (int)o["k"];
+      l.stall_from = 15000;
+      l.stall_to = l.stall_from + 1000000;
+      const char* e = k > 64 ? batch<2>(g, k, l, o["stall"] > 0) : batch<1>(g, k, l, o["stall"] > 0);
+      if (e) return failed(e, seed);
+      continue;
+    }
     std::vector<int> dist(g.n, -1);
     dist[s] = 0;
     const int nw = (g.n + 63) / 64;

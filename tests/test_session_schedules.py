@@ -68,3 +68,15 @@ def test_long_path_before_wide_levels(emu, kind, small):
     """Levels of one workgroup, or of one cluster, for several times the wait that
     workgroups without work are given, then levels that need them."""
     emu(kind, 1, 4, grid=40, ticks=6000, path=300, levels=320, small=small, wide=400, wmax=3)
+
+
+@pytest.mark.parametrize("k", [40, 100])
+def test_batch(emu, k):
+    emu("batch", 1, 4, grid=20, levels=40, wide=30, k=k)
+    emu("batch", 1, 4, grid=20, levels=40, wide=30, k=k, hold=0.0003, held=20000)
+
+
+def test_batch_goes_on_and_times_out(emu):
+    """A run that stopped for more level planes goes on and a wait of its times out: it
+    must not look stopped for planes again."""
+    emu("batch", 1, 4, grid=20, levels=14, wide=30, stall=1)
