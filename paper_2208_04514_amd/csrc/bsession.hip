@@ -80,6 +80,8 @@ __device__ __forceinline__ u64 compress(u64 x) {
 template <int P>
 struct BatchPolicy {
   static constexpr int kPiece = 64;
+  // (the planes are read and written by their nodes' owner at every level)
+  static constexpr bool kAdmits = false;
   using Args = BsArgs;
   struct State {
     unsigned level;             // being run

@@ -190,9 +190,9 @@ constexpr int kSessGroup = 32;        // workgroups (consecutive ranks) per grou
 constexpr int kSessStripes = 4;       // sub-queues of a frontier
 constexpr int kSessSegs = kSessGroup + 1;   // segments of a frontier's queue at most
 constexpr int kSessRec = 64;          // words of a level record
-constexpr int kPiece = 64;           // edges per queue entry: longer rows take several
 constexpr int kSessPerCu = 4;         // workgroups per compute unit
-constexpr unsigned long long kJoinTicks = 500;   // 100 MHz ticks the member list stays open
+// 100 MHz ticks that the first level which needs others waits for them at most
+constexpr unsigned long long kJoinTicks = 500;
 
 // A barrier group's counters of one level: nodes found, their out-edges,
 // adjacency entries examined, each with the arrivals in its top 16 bits (the
@@ -219,7 +219,8 @@ struct SessSlot {
 struct SessCtrl {
   SessSlot slot[3];
   SessWord joined[kSessGroups];       // bit per workgroup that has started
-  alignas(kLine) unsigned memb[kSessGroups];   // those in the session
+  // rank + 1 of each workgroup that has one, unless all had from the start
+  alignas(kLine) unsigned rank1[kSessGroups * kSessGroup];
   alignas(kLine) u64 rec[kSessRec];   // the level record (tag in the high half)
   SessReport crec[2][kSessGroup];     // cluster levels, by level parity: each member's line
   SessStripe over[3];                 // cluster levels, by level % 3: entries past a segment

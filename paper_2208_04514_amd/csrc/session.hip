@@ -190,6 +190,7 @@ __device__ __forceinline__ void sess_pull(const SsspArgs& a, int* rank_lane, int
 // Queue entries are (row start, out-degree).
 struct HopPolicy {
   static constexpr int kPiece = kHopPiece;
+  static constexpr bool kAdmits = true;
   using Args = SsspArgs;
   // LevelState's fields
   struct State {

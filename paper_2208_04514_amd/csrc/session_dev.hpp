@@ -12,6 +12,7 @@
 //   P::scans(p)             the level sums c.scan
 //   P::words(a)             64-node words of a scan level
 //   P::kPiece               edges per queue entry
+//   P::kAdmits              a level may have more members than the one before
 //   P::advance(a, sh, nf, mf, scan, record)  wave 0, uniform arguments: the
 //                             next level's plan from the sums over the
 //                             workgroups (set_plan)
@@ -45,8 +46,12 @@
 //
 // Membership.  A barrier may only count workgroups that are running, and a
 // plain launch promises nothing about that.  So each workgroup joins with an
-// atomic when it starts; workgroup 0 closes the list when the first level
-// that needs others comes up; whoever starts later leaves at once.  Every
+// atomic when it starts; workgroup 0 gives ranks to those that have, when the
+// first level that needs others comes up (after a short wait), and to later ones
+// ahead of each level: beside other work on the device few may start with the
+// launch.  (Two callers on R-MAT 20, weighted: with the first list kept for the whole
+// run one call in 20 took 50 ms instead of 2.)  A rank is kept for good, so that
+// whoever is behind still belongs where it did.  Every
 // wait is on workgroups that have joined, hence on running ones, and is
 // bounded besides.  The bound is on a wait for the next record, so a long run of
 // solo or cluster levels publishes one now and then.
@@ -73,12 +78,15 @@ constexpr int kClusterEdges = 32768;
 constexpr int kClusterWords = 1024;
 // Grid push: frontier edges per workgroup taking part (half a step of 64 a wave).
 constexpr int kEdgesPerWg = 256;
-constexpr u64 kClosed = 1ull << 63;
 // Solo or cluster levels between two records at most: some 15 ms, against the 10 s
 // that workgroups without work wait for one.
 constexpr unsigned kRecordLevels = 4096;
 
 enum SessMode { kModeGrid = 1, kModeCluster = 2, kModeSolo = 3, kModeEnd = 4 };
+
+// kNoRanks: no level has needed others yet.  kLaunchRanks: everyone had started when
+// the first did.
+enum SessRanks { kNoRanks = 0, kListed = 1, kLaunchRanks = 2 };
 
 // The level to run: the policy's state, how it runs, and where its frontier's
 // queue is.  32-bit words throughout, kept in LDS in the layout of the level
@@ -91,7 +99,8 @@ struct SessPlan {
   unsigned fe;                        // out-edges of the frontier
   unsigned qp;                        // the queue's parity
   unsigned stride;                    // entries between its segments
-  unsigned full;                      // every workgroup of the launch has joined
+  unsigned members;                   // workgroups with a rank (before any: of the launch)
+  unsigned ranks;                     // where ranks stand (SessRanks)
   unsigned scan;                      // a level over all nodes, not over the queue
   unsigned seg_n[kSessSegs];          // entries of each segment
 };
@@ -108,7 +117,10 @@ struct SessQueue {
   u64 stage[kStage];
   int own[kSW][4 * kWave];            // per wave: which row an edge belongs to
   unsigned pre_g[kSessSegs + 1];      // first group of 64 entries of each segment
-  unsigned rank, members;
+  unsigned rank;
+  unsigned listed[kSessGroups];       // workgroup 0: those with a rank, as `joined`
+  int all;                            // workgroup 0: every workgroup has joined, as far as
+                                      //   it looked
   int go, ok;
   unsigned gb;                        // where the staged entries go in the sub-queue
   unsigned nf, mf, scan, n_out;       // this level's counters
@@ -145,7 +157,7 @@ __device__ __forceinline__ unsigned uniform(unsigned x) {
 template <class P>
 __device__ __forceinline__ void set_plan(SessShared<P>& sh, bool end, bool scan, u64 fe, int words,
                                          int solo_edges) {
-  unsigned K = min(sh.members, (unsigned)kSessGroup), mode;
+  unsigned K = min(sh.p.members, (unsigned)kSessGroup), mode;
   if (end) {
     mode = kModeEnd;
   } else if (!scan && fe <= (u64)min(solo_edges, kSoloCap)) {
@@ -156,7 +168,7 @@ __device__ __forceinline__ void set_plan(SessShared<P>& sh, bool end, bool scan,
     const unsigned want = scan ? (unsigned)((words + kSW - 1) / kSW)
                                : (unsigned)((fe + kEdgesPerWg - 1) / kEdgesPerWg);
     mode = kModeGrid;
-    K = min(sh.members, max(want, 1u));
+    K = min(sh.p.members, max(want, 1u));
   }
   if (lane_id() == 0) {
     sh.p.step += 1;
@@ -226,18 +238,13 @@ __device__ __forceinline__ unsigned sess_poll(SessCtrl* sc, SessShared<P>& sh, u
   }
 }
 
-// Wave 0: rank and member count from the closed list (lane w holds word w).
-__device__ __forceinline__ void sess_rank(const unsigned word, SessQueue& sh, unsigned wi,
-                                          unsigned bi) {
-  const int c = __popc(word);
-  const int incl = wave_incl_scan(c);
-  const unsigned mine = (unsigned)__shfl((int)word, (int)wi, kWave);
-  const unsigned before = (unsigned)__shfl(incl - c, (int)wi, kWave);
-  const unsigned all = (unsigned)__builtin_amdgcn_readlane(incl, kWave - 1);
-  if (lane_id() == 0) {
-    sh.rank = before + (unsigned)__popc(mine & ((1u << bi) - 1u));
-    sh.members = all;
-  }
+// Workgroups are numbered by layer, XCD and position there (consecutive ones go to
+// the 8 XCDs in turn): word (layer, XCD), bit = position, so that 32 consecutive
+// ranks share an XCD's L2.
+__device__ __forceinline__ unsigned word_of(unsigned b) { return (b >> 8) * 8 + (b & 7); }
+__device__ __forceinline__ unsigned bit_of(unsigned b) { return (b >> 3) & 31; }
+__device__ __forceinline__ unsigned workgroup_of(unsigned word, unsigned bit) {
+  return (word >> 3) * 256 + bit * 8 + (word & 7);
 }
 
 // Lane w: the workgroups of a launch of `grid` that have word w, as its bits.
@@ -245,6 +252,48 @@ __device__ __forceinline__ unsigned launch_word(int w, unsigned grid) {
   const int left = (int)grid - (w >> 3) * 256 - (w & 7);
   const int cnt = min((left + 7) >> 3, 32);
   return w >= kSessGroups || cnt <= 0 ? 0u : cnt == 32 ? ~0u : (1u << cnt) - 1u;
+}
+
+// Wave 0: workgroup b's rank if every workgroup has one.
+__device__ __forceinline__ unsigned launch_rank(unsigned b) {
+  const unsigned word = launch_word(lane_id(), gridDim.x);
+  const int c = __popc(word);
+  const unsigned before = (unsigned)__shfl(wave_incl_scan(c) - c, (int)word_of(b), kWave);
+  return before + bit_of(b);
+}
+
+// Workgroup 0, wave 0 (lane w: word w): how many have joined.
+__device__ __forceinline__ unsigned joined_count(SessCtrl* sc) {
+  const unsigned w = lane_id() < kSessGroups ? (unsigned)ld_relaxed(&sc->joined[lane_id()].w) : 0u;
+  return wave_sum((unsigned)__popc(w)) + 1;        // (itself does not)
+}
+
+// Workgroup 0, wave 0: ranks for those that have joined since.  True if any; they
+// are in place then.
+template <class P>
+__device__ __forceinline__ bool sess_admit(SessCtrl* sc, SessShared<P>& sh) {
+  const int lane = lane_id();
+  const bool in = lane < kSessGroups;
+  unsigned w = in ? (unsigned)ld_relaxed(&sc->joined[lane].w) : 0u;
+  if (lane == 0) w |= 1u;
+  const unsigned fresh = in ? w & ~sh.listed[lane] : 0u;
+  const int c = __popc(fresh);
+  const int incl = wave_incl_scan(c);
+  const unsigned added = (unsigned)__builtin_amdgcn_readlane(incl, kWave - 1);
+  if (!added) return false;
+  const unsigned had = uniform(sh.p.ranks) == kNoRanks ? 0u : uniform(sh.p.members);
+  unsigned r = had + (unsigned)(incl - c);
+  for (unsigned f = fresh; f; f &= f - 1)
+    st_relaxed(&sc->rank1[workgroup_of((unsigned)lane, (unsigned)__builtin_ctz(f))], ++r);
+  if (in) sh.listed[lane] = w;
+  if (lane == 0) {
+    sh.p.members = had + added;
+    sh.p.ranks = kListed;
+    sh.all = had + added >= gridDim.x;
+  }
+  wait_all();
+  wave_sync();
+  return true;
 }
 
 struct SessCount {
@@ -505,6 +554,7 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
         }
       }
       if (ok) {
+        if (P::kAdmits && !uniform((unsigned)sh.all)) sess_admit(sc, sh);
         const unsigned sq = lane < kSessStripes ? ld_relaxed(&slot->q[lane].n) : 0u;
         constexpr u64 low = (1ull << 48) - 1;
         const u64 nf = wave_sum(w0 & low), mf = wave_sum(w1 & low);
@@ -638,11 +688,9 @@ __device__ __forceinline__ void solo_run(const typename P::Args& a, const SessAr
       add_counts(sh, c, false);
       keep(ahead);        // (of the level before)
       ahead = c.ahead;
-      if (wv == kSW - 1 && !sh.p.full) {
+      if (wv == kSW - 1 && !sh.all) {
         // the wave that is first out of work looks who has joined
-        const u64 w = lane < kSessGroups ? ld_relaxed(&x.sc->joined[lane].w) : 0ull;
-        const unsigned cnt = wave_sum((unsigned)__popcll(w));
-        if (lane == 0 && cnt + 1 >= gridDim.x) sh.p.full = 1;
+        if (sh.p.ranks == kNoRanks && joined_count(x.sc) >= gridDim.x && lane == 0) sh.all = 1;
       }
     }
     __syncthreads();
@@ -683,20 +731,20 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
   const int t = threadIdx.x, lane = lane_id();
   const unsigned bid = blockIdx.x;
   SessCtrl* sc = x.sc;
-  // consecutive workgroups go to the 8 XCDs in turn: word (layer, XCD), bit =
-  // position on that XCD, so that 32 consecutive ranks share an XCD's L2
-  const unsigned wi = (bid >> 8) * 8 + (bid & 7), bi = (bid >> 3) & 31;
   if (t == 0) {
     sh.nf = sh.mf = sh.scan = sh.n_out = 0;
     sh.ok = 1;
-    if (bid != 0 && (atom_or(&sc->joined[wi].w, 1ull << bi) & kClosed)) sh.ok = 0;
+    sh.all = 0;
+    if (bid != 0) atom_or(&sc->joined[word_of(bid)].w, 1ull << bit_of(bid));
   }
-  // the rank if every workgroup joins
-  if (t < kWave) sess_rank(launch_word(lane, gridDim.x), sh, wi, bi);
+  if (t < kSessGroups) sh.listed[t] = 0;
+  if (t < kWave) {
+    const unsigned r = launch_rank(bid);
+    if (lane == 0) sh.rank = r;
+  }
   __syncthreads();
-  if (!sh.ok) return;
   unsigned gen = 0;
-  bool ranked = false, lead = false;    // lead: workgroup 0 holds the next plan
+  bool ranked = bid == 0, lead = false;    // lead: workgroup 0 holds the next plan
   if (bid == 0) {
     if (t < kWave) {
       if (lane == 0) {
@@ -704,7 +752,8 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
         sh.p.mode = 0;
         sh.p.qp = 0;
         sh.p.stride = x.qcap;
-        sh.p.full = 0;
+        sh.p.members = gridDim.x;
+        sh.p.ranks = kNoRanks;
       }
       wave_sync();
       P::begin(a, x, sh);
@@ -725,52 +774,39 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
   }
   for (;;) {
     if (lead) {
-      // close the member list the first time, then publish the plan
       if (t < kWave) {
-        if (sh.p.mode != kModeEnd && sh.p.mode != kModeSolo && !ranked) {
-          bool full = sh.p.full != 0;
-          while (!full) {
-            const u64 w = lane < kSessGroups ? ld_relaxed(&sc->joined[lane].w) : 0ull;
-            const unsigned cnt = wave_sum((unsigned)__popcll(w));
-            full = cnt + 1 >= gridDim.x;
-            if (wall_clock64() - t_start > kJoinTicks) break;
-          }
-          if (!full) {
-            unsigned w = 0;
-            if (lane < kSessGroups) {
-              w = (unsigned)atom_or(&sc->joined[lane].w, kClosed);
-              if (lane == 0) w |= 1u;
-              st_relaxed(&sc->memb[lane], w);
-            }
-            sess_rank(w, sh, 0, 0);
-            wait_all();
-          }
-          if (lane == 0) sh.p.full = full ? 1 : 0;
-          wave_sync();
-          // the plan was made without knowing the members
-          if (!full) {
-            const unsigned fe = uniform(sh.p.fe);
-            set_plan<P>(sh, false, sh.p.scan != 0, fe, P::words(a), 0);
-          }
+        const unsigned mode = uniform(sh.p.mode);
+        bool more = false;
+        if (mode == kModeEnd || mode == kModeSolo) {
+        } else if (uniform(sh.p.ranks) == kNoRanks) {
+          // the first level that needs others
+          bool all = uniform((unsigned)sh.all) != 0;
+          while (!all && wall_clock64() - t_start <= kJoinTicks) all = joined_count(sc) >= gridDim.x;
+          if (!all) more = sess_admit(sc, sh);
+          else if (lane == 0) sh.p.ranks = kLaunchRanks, sh.all = 1;
+        } else if (P::kAdmits && !uniform((unsigned)sh.all)) {
+          more = sess_admit(sc, sh);
         }
+        // the plan was made for other members
+        if (more) set_plan<P>(sh, false, sh.p.scan != 0, uniform(sh.p.fe), P::words(a), 0);
         sess_publish(sc, sh, gen + 1);
       }
-      ranked = ranked || (sh.p.mode != kModeEnd && sh.p.mode != kModeSolo);
       gen += 1;
       lead = false;
       __syncthreads();
     }
     if (sh.p.mode == kModeEnd) return;
-    if (!ranked && sh.p.mode != kModeSolo) {
-      if (!sh.p.full) {
+    if (!ranked && sh.p.ranks != kNoRanks) {
+      if (sh.p.ranks == kListed) {
         __syncthreads();
-        if (t < kWave)
-          sess_rank(lane < kSessGroups ? ld_relaxed(&sc->memb[lane]) : 0u, sh, wi, bi);
+        if (t == 0) sh.rank = ld_relaxed(&sc->rank1[bid]) - 1u;     // (none: the largest)
         __syncthreads();
       }
-      ranked = true;
+      ranked = sh.rank != ~0u;
+      if (!ranked && !P::kAdmits) return;
     }
-    const bool mine = sh.p.mode == kModeSolo ? bid == 0 : sh.rank < sh.p.K;
+    // (a rank given since the record is past its members)
+    const bool mine = sh.p.mode == kModeSolo ? bid == 0 : ranked && sh.rank < sh.p.K;
     bool poll = !mine;
     if (mine && sh.p.mode == kModeGrid) {
       gen = grid_level(a, x, sh, gen);

@@ -140,6 +140,7 @@ enum WPhase {
 // Queue entries are (node, piece of its row).
 struct WeightPolicy {
   static constexpr int kPiece = kWeightPiece;
+  static constexpr bool kAdmits = true;
   using Args = WArgs;
   struct State {
     unsigned phase, par;        // par: membership bitmap of the frontier

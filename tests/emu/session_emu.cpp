@@ -1,5 +1,6 @@
 // The session frame and its policies on the host, under random schedules:
 // session_emu hop|weighted|batch SEED0 SEEDS [grid=N hold=P held=N late=P ...].
+// join: every workgroup has to be a member in the end.
 // Prints one line and exits nonzero at the first run whose distances or totals
 // differ from a plain search's.
 #include <hip/hip_runtime.h>
@@ -107,6 +108,12 @@ struct Queues {
   }
 };
 
+// Members of the last record.
+template <class P>
+static unsigned members(const SessCtrl& sc) {
+  return (unsigned)sc.rec[offsetof(SessPlan<typename P::State>, members) / 4];
+}
+
 static int failed(const char* what, unsigned long long seed) {
   printf("seed %llu: %s\n", seed, what);
   return 1;
@@ -190,7 +197,8 @@ int main(int argc, char** argv) {
   const int seeds = atoi(argv[3]);
   std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},
                                   {"levels", 60}, {"wide", 120}, {"small", 6}, {"wmax", 40},
-                                  {"ticks", 0.02}, {"mode", 3}, {"path", 0}, {"k", 40}, {"stall", 0}};
+                                  {"ticks", 0.02}, {"mode", 3}, {"path", 0}, {"k", 40}, {"stall", 0},
+                                  {"join", 0}, {"after", 400000}};
   for (int i = 4; i < argc; ++i) {
     const std::string a = argv[i];
     const size_t eq = a.find('=');
@@ -219,7 +227,7 @@ int main(int argc, char** argv) {
     const double late = o["late"];
     std::vector<unsigned long long> start(l.grid, 0);
     for (unsigned b = 1; b < l.grid; ++b)
-      if ((double)(rnd() % 1000) < late * 1000) start[b] = rnd() % 400000;
+      if ((double)(rnd() % 1000) < late * 1000) start[b] = rnd() % (unsigned)o["after"];
     l.start = [&](unsigned b) { return start[b]; };
 
     if (kind == "batch") {
@@ -260,6 +268,7 @@ int main(int argc, char** argv) {
       most = std::max(most, used);
       const LevelState& st = ctrl->st[1];
       if (st.done != 1) return failed("not done", seed);
+      if (o["join"] > 0 && members<HopPolicy>(*sc) < l.grid) return failed("members", seed);
       if (st.reached != (u64)reached || st.source_edges != (u64)edges) return failed("totals", seed);
     } else {
       std::unique_ptr<WCtrl> ctrl(new WCtrl());
@@ -296,6 +305,7 @@ int main(int argc, char** argv) {
           emu::run(l, [&](unsigned b) { session<WeightPolicy>(a, q.x, *sh[b]); });
       if (!used) return failed("no end", seed);
       most = std::max(most, used);
+      if (o["join"] > 0 && members<WeightPolicy>(ctrl->sess) < l.grid) return failed("members", seed);
       if (ctrl->done != 1) return failed(ctrl->done == 2 ? "too many levels" : "not done", seed);
     }
     if (dist != want) return failed("distances", seed);

@@ -80,3 +80,15 @@ def test_batch_goes_on_and_times_out(emu):
     """A run that stopped for more level planes goes on and a wait of its times out: it
     must not look stopped for planes again."""
     emu("batch", 1, 4, grid=20, levels=14, wide=30, stall=1)
+
+
+@pytest.mark.parametrize("kind", ["hop", "weighted", "batch"])
+def test_late_workgroups(emu, kind):
+    """Workgroups that start while the levels run."""
+    emu(kind, 1, 8, grid=40 if kind != "batch" else 20, late=0.8, levels=40)
+    emu(kind, 1, 8, grid=40 if kind != "batch" else 20, late=0.8, levels=40, hold=0.0003, held=20000)
+
+
+@pytest.mark.parametrize("kind", ["hop", "weighted"])
+def test_late_workgroups_take_part(emu, kind):
+    emu(kind, 1, 4, late=0.9, after=100000, levels=60, small=0, join=1)
