@@ -364,6 +364,7 @@ dawn_status dawn_sssp_weighted(dawn_ctx* c, int32_t graph, int32_t source, int32
   if (source < 0 || source >= g->n)
     return fail(DAWN_E_INVALID_ARG, "source %d outside [0, %d)", source, g->n);
   DAWN_HIP(hipSetDevice(ctx->device));
+  const Caller caller(ctx);
   return wsssp_run(ctx, g.get(), source, dist, (flags & DAWN_DEVICE_OUT) != 0, stats);
 }
 
@@ -417,6 +418,7 @@ dawn_status dawn_sssp(dawn_ctx* c, int32_t graph, int32_t source, int32_t* dist,
     std::lock_guard<std::mutex> lk(g->mu);
     p = g->params;
   }
+  const Caller caller(ctx);
   return sssp_run(ctx, g.get(), p, source, dist, (flags & DAWN_DEVICE_OUT) != 0, stats);
 }
 
@@ -436,6 +438,7 @@ dawn_status dawn_sssp_noalloc(dawn_ctx* c, int32_t graph, int32_t source, int32_
     std::lock_guard<std::mutex> lk(g->mu);
     p = g->params;
   }
+  const Caller caller(ctx);
   return sssp_run_noalloc(ctx, g.get(), p, source, d_dist,
                           reinterpret_cast<hipStream_t>(hip_stream), stats);
 }
@@ -467,6 +470,7 @@ dawn_status dawn_mssp(dawn_ctx* c, int32_t graph, const int32_t* sources, int32_
     std::lock_guard<std::mutex> lk(g->mu);
     p = g->params;
   }
+  const Caller caller(ctx);
   return mssp_run(ctx, g.get(), p, sources, k, dist, (flags & DAWN_DEVICE_OUT) != 0, g->n, stats);
 }
 
@@ -522,6 +526,7 @@ dawn_status dawn_apsp_wcc(dawn_ctx* c, int32_t graph, int32_t* wcc_nodes, int32_
   }
   const int32_t S = (int32_t)nodes.size();
   if (dist && S > 0) {
+    const Caller caller(ctx);
     std::vector<int32_t> srcs(S);
     for (int32_t i = 0; i < S; ++i) srcs[i] = i;   // subgraph ids are WCC ranks
     DAWN_TRY(mssp_run(ctx, sub.get(), p, srcs.data(), S, dist, (flags & DAWN_DEVICE_OUT) != 0, S,

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -384,10 +385,45 @@ struct Ctx {
   int32_t next_graph = 0;
   Server* server = nullptr;
   std::mutex server_mu;
+  // calls in flight, when that were last two, three and four at a call's start, and
+  // when work was last queued that no call waits for (Caller, ctx_share)
+  std::atomic<int> callers{0};
+  std::atomic<uint64_t> crowd_ns[3] = {};
+  std::atomic<uint64_t> queued_ns{0};
   std::mutex bounce_mu;
   std::vector<Bounce*> bounces;            // idle pinned buffers (hostcopy.cpp)
   int bounce_count = 0;                    // idle and taken
 };
+
+// A call that runs work on the device.
+constexpr int kMaxShare = 4;             // as many kernels run side by side (hardware queues)
+constexpr uint64_t kCrowdNs = 2000000;   // how long two calls that met count as sharing
+struct Caller {
+  explicit Caller(Ctx* c) : ctx(c) {
+    const int n = std::min(ctx->callers.fetch_add(1) + 1, kMaxShare);
+    if (n == 1) return;
+    const uint64_t now = now_ns();
+    for (int i = 2; i <= n; ++i) ctx->crowd_ns[i - 2].store(now, std::memory_order_relaxed);
+  }
+  ~Caller() { ctx->callers.fetch_sub(1); }
+  Caller(const Caller&) = delete;
+  Caller& operator=(const Caller&) = delete;
+  Ctx* ctx;
+};
+// How many the device is to be shared by, this call included: those in flight, or
+// seen together just before (threads that call in turn are between two calls now
+// and then), and work queued without a call to wait for it.
+inline int ctx_share(const Ctx* ctx, bool queued = true) {
+  const uint64_t now = now_ns();
+  auto recent = [now](const std::atomic<uint64_t>& t) {
+    return now - t.load(std::memory_order_relaxed) < kCrowdNs;
+  };
+  int n = std::max(ctx->callers.load(std::memory_order_relaxed), 1);
+  for (int i = kMaxShare; i > n; --i)
+    if (recent(ctx->crowd_ns[i - 2])) n = i;
+  if (queued && recent(ctx->queued_ns)) ++n;
+  return std::min(n, kMaxShare);
+}
 
 // hostcopy.cpp: `rows` rows of n values, one after another on the device, to rows
 // dst_stride values apart on the host, after the stream's work; returns when they

@@ -312,6 +312,7 @@ static bool may_admit(const Server* S, const Engine* e) {
 
 // Launch seeds (if any) and the next level of engine e.  S->mu held.
 static dawn_status launch_level(Server* S, Engine* e) {
+  S->ctx->queued_ns.store(now_ns(), std::memory_order_relaxed);
   BatchWs* w = e->ws;
   hipStream_t s = w->stream;
   const GraphRec* g = e->g.get();

@@ -848,13 +848,19 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
   }
 }
 
-// Workgroups of a session's launch: per_cu per compute unit, but no more than a
-// level can use (words: 64-node words of a scan level; m: edges).
-inline int sess_grid(const Ctx* ctx, int per_cu, int words, long long m) {
+// Workgroups of a session's launch: per_cu per compute unit, divided by `share`, but no
+// more than a level can use (words: 64-node words of a scan level; m: edges).  A
+// session holds what it has to its end, so calls that share the device (ctx_share)
+// take a part each: sessions that take all of it run one after another, and whoever
+// comes next starts with what the last one left.
+// Calls a second by one, two and four callers, with all of it to each and now: R-MAT 20
+// 10,900, 7,800, 7,400 and 10,800, 14,500, 14,700 (a launch per level: 5,300, 6,000,
+// 5,700); R-MAT 17 beside a caller on a long grid 320 and 17,000 (3,800).
+inline int sess_grid(const Ctx* ctx, int per_cu, int share, int words, long long m) {
   const long long useful = std::max<long long>((words + kSW - 1) / kSW,
                                                (m + kEdgesPerWg - 1) / kEdgesPerWg);
   return (int)std::max<long long>(
-      1, std::min<long long>({useful, (long long)per_cu * ctx->num_cu,
+      1, std::min<long long>({useful, (long long)std::max(per_cu * ctx->num_cu / share, kSessGroup),
                               (long long)kSessGroups * kSessGroup}));
 }
 

@@ -790,7 +790,7 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL(wsssp_init, dim3(fill), dim3(kSB), 0, s, a, source);
-    hipLaunchKernelGGL(wsssp_session, dim3(sess_grid(ctx, std::min(occ, kSessPerCu), a.nw, g->m)),
+    hipLaunchKernelGGL(wsssp_session, dim3(sess_grid(ctx, std::min(occ, kSessPerCu), ctx_share(ctx), a.nw, g->m)),
                        dim3(kSB), 0, s, a, x);
     hipLaunchKernelGGL(wsssp_close, dim3(fill), dim3(kSB), 0, s, a);
     e = hipGetLastError();

@@ -191,8 +191,43 @@ static const char* batch(const Graph& g, int k, emu::Launch l, bool stall) {
   return reached == fc->part[0].reached ? nullptr : "totals";
 }
 
+// The part of the device that a call's session may take.
+static const char* callers() {
+  Ctx c;
+  auto pause = [](int ms) { std::this_thread::sleep_for(std::chrono::milliseconds(ms)); };
+  if (ctx_share(&c) != 1) return "idle";
+  {
+    Caller one(&c);
+    if (ctx_share(&c) != 1) return "one caller";
+  }
+  for (int i = 0; i < 3; ++i) {
+    Caller one(&c);
+    if (ctx_share(&c) != 1) return "one caller, again and again";
+  }
+  {
+    Caller one(&c), two(&c);
+    if (ctx_share(&c) != 2) return "two callers";
+    Caller three(&c), four(&c), five(&c);
+    if (ctx_share(&c) != kMaxShare) return "five callers";
+  }
+  if (ctx_share(&c) != kMaxShare) return "just after";
+  pause(5);
+  {
+    Caller one(&c);
+    if (ctx_share(&c) != 1) return "later";
+    c.queued_ns = now_ns();
+    if (ctx_share(&c) != 2 || ctx_share(&c, false) != 1) return "beside queued work";
+  }
+  pause(5);
+  return ctx_share(&c) != 1 || c.callers != 0 ? "in the end" : nullptr;
+}
+
 int main(int argc, char** argv) {
   const std::string kind = argv[1];
+  if (kind == "callers") {
+    const char* e = callers();
+    return e ? failed(e, 0) : 0;
+  }
   const unsigned long long seed0 = strtoull(argv[2], nullptr, 10);
   const int seeds = atoi(argv[3]);
   std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},

@@ -92,3 +92,7 @@ def test_late_workgroups(emu, kind):
 @pytest.mark.parametrize("kind", ["hop", "weighted"])
 def test_late_workgroups_take_part(emu, kind):
     emu(kind, 1, 4, late=0.9, after=100000, levels=60, small=0, join=1)
+
+
+def test_callers_share_the_device(emu):
+    emu("callers", 0, 1, jobs=1)
