@@ -73,6 +73,25 @@ void dev_free(Ctx* ctx, void* p, size_t bytes) {
   if (ctx && bytes) ctx->used.fetch_sub(bytes == 0 ? 1 : bytes);
 }
 
+dawn_status StreamLease::take() {
+  std::lock_guard<std::mutex> lk(ctx->stream_mu);
+  int best = 0;
+  for (int i = 1; i < kMaxShare; ++i)
+    if (ctx->streams[i].users < ctx->streams[best].users) best = i;
+  if (!ctx->streams[best].s)
+    DAWN_HIP(hipStreamCreateWithFlags(&ctx->streams[best].s, hipStreamNonBlocking));
+  ++ctx->streams[best].users;
+  at = best;
+  s = ctx->streams[best].s;
+  return DAWN_OK;
+}
+
+StreamLease::~StreamLease() {
+  if (at < 0) return;
+  std::lock_guard<std::mutex> lk(ctx->stream_mu);
+  --ctx->streams[at].users;
+}
+
 dawn_status get_graph(Ctx* ctx, int32_t id, std::shared_ptr<GraphRec>* out) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   auto it = ctx->graphs.find(id);
@@ -233,6 +252,8 @@ dawn_status dawn_destroy(dawn_ctx* c) {
     ctx->graphs.clear();
   }
   hipDeviceSynchronize();
+  for (auto& x : ctx->streams)
+    if (x.s) hipStreamDestroy(x.s);
   bounces_free(ctx);
   delete ctx;
   return DAWN_OK;

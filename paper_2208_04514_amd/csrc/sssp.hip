@@ -1337,9 +1337,8 @@ static LevelKernel level_kernel(const SsspArgs& a) {
 }
 
 SsspWs::~SsspWs() {
-  // a direct-launch traversal returns once its end is reported, while level
-  // launches queued past the end (they only carry the final state) may still
-  // be running on this stream
+  // a traversal returns once its end is reported, while the launch that reported it
+  // may still be running
   if (stream) hipStreamSynchronize(stream);
   if (gexec) hipGraphExecDestroy(gexec);
   if (gexec_more) hipGraphExecDestroy(gexec_more);
@@ -1359,12 +1358,13 @@ SsspWs::~SsspWs() {
   if (h_m) hipHostFree(h_m);
   if (ev0) hipEventDestroy(ev0);
   if (ev1) hipEventDestroy(ev1);
-  if (stream) hipStreamDestroy(stream);
 }
 
-static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out) {
+static dawn_status ws_create(Ctx* ctx, GraphRec* g, hipStream_t stream,
+                             std::unique_ptr<SsspWs>* out) {
   std::unique_ptr<SsspWs> w(new SsspWs());
   w->ctx = ctx;
+  w->stream = stream;
   const int n = g->n;
   const size_t nw = ((size_t)n + 63) / 64;
   // chunk lists: every node of out-degree >= 64 could be "big" at the smallest
@@ -1405,8 +1405,7 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, std::unique_ptr<SsspWs>* out
                          hipHostMallocCoherent | hipHostMallocMapped));
   memset(w->h_m, 0, sizeof(HostMirror));
   DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
-  DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
-  // on the workspace's stream: hipMemset returns before it has run, in the null
+  // on the call's stream: hipMemset returns before it has run, in the null
   // stream, and could clear the block in the middle of the first traversal
   DAWN_HIP(hipMemsetAsync(w->ctrl, 0, ctrl_bytes + sizeof(SessCtrl), w->stream));
   DAWN_HIP(hipEventCreate(&w->ev0));
@@ -1763,7 +1762,15 @@ dawn_status sssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, int32_t source
       g->sssp_pool.pop_back();
     }
   }
-  if (!w) DAWN_TRY(ws_create(ctx, g, &w));
+  StreamLease lease(ctx);
+  DAWN_TRY(lease.take());
+  if (!w) {
+    DAWN_TRY(ws_create(ctx, g, lease.s, &w));
+  } else if (w->stream != lease.s) {
+    // (its last launch may still be running)
+    DAWN_HIP(hipStreamWaitEvent(lease.s, w->ev1, 0));
+    w->stream = lease.s;
+  }
   struct Return {
     GraphRec* g;
     std::unique_ptr<SsspWs>& w;

@@ -603,7 +603,7 @@ namespace {
 
 struct WWs {
   Ctx* ctx = nullptr;
-  hipStream_t stream = nullptr;
+  hipStream_t stream = nullptr;         // of the call that has the workspace
   hipEvent_t ev1 = nullptr;
   u64* q[2] = {nullptr, nullptr};
   u64* inq[2] = {nullptr, nullptr};
@@ -627,7 +627,6 @@ struct WWs {
     if (ctx) ctx->used -= bytes;
     if (h_m) hipHostFree(h_m);
     if (ev1) hipEventDestroy(ev1);
-    if (stream) hipStreamDestroy(stream);
   }
 };
 
@@ -652,7 +651,6 @@ dawn_status wws_create(Ctx* ctx, const GraphRec* g, std::unique_ptr<WWs>* out) {
                          hipHostMallocCoherent | hipHostMallocMapped));
   memset(w->h_m, 0, sizeof(WMirror));
   DAWN_HIP(hipHostGetDevicePointer((void**)&w->d_m, w->h_m, 0));
-  DAWN_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
   DAWN_HIP(hipEventCreateWithFlags(&w->ev1, hipEventDisableTiming));
   *out = std::move(w);
   return DAWN_OK;
@@ -737,7 +735,12 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
       pool->ws.pop_back();
     }
   }
+  StreamLease lease(ctx);
+  DAWN_TRY(lease.take());
   if (!w) DAWN_TRY(wws_create(ctx, g, &w));
+  // (a pooled workspace's last launch may still be running)
+  else if (w->stream != lease.s) DAWN_HIP(hipStreamWaitEvent(lease.s, w->ev1, 0));
+  w->stream = lease.s;
   WArgs a;
   memset(&a, 0, sizeof(a));
   a.n = g->n;
