@@ -82,6 +82,10 @@ struct BatchPolicy {
   static constexpr int kPiece = 64;
   // (the planes are read and written by their nodes' owner at every level)
   static constexpr bool kAdmits = false;
+  template <class Plan>
+  static __device__ __forceinline__ unsigned long long join_ticks(const Plan&, int) {
+    return kJoinLong;
+  }
   using Args = BsArgs;
   struct State {
     unsigned level;             // being run

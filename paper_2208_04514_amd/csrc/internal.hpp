@@ -192,8 +192,10 @@ constexpr int kSessStripes = 4;       // sub-queues of a frontier
 constexpr int kSessSegs = kSessGroup + 1;   // segments of a frontier's queue at most
 constexpr int kSessRec = 64;          // words of a level record
 constexpr int kSessPerCu = 4;         // workgroups per compute unit
-// 100 MHz ticks that the first level which needs others waits for them at most
+// 100 MHz ticks that the first level which needs others waits for them; where those are
+// the run's for good, kJoinLong
 constexpr unsigned long long kJoinTicks = 500;
+constexpr unsigned long long kJoinLong = 20000;
 
 // A barrier group's counters of one level: nodes found, their out-edges,
 // adjacency entries examined, each with the arrivals in its top 16 bits (the

@@ -191,6 +191,10 @@ __device__ __forceinline__ void sess_pull(const SsspArgs& a, int* rank_lane, int
 struct HopPolicy {
   static constexpr int kPiece = kHopPiece;
   static constexpr bool kAdmits = true;
+  template <class Plan>
+  static __device__ __forceinline__ unsigned long long join_ticks(const Plan& p, int words) {
+    return admit_ticks(p, words);
+  }
   using Args = SsspArgs;
   // LevelState's fields
   struct State {

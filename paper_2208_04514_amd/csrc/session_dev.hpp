@@ -13,6 +13,7 @@
 //   P::words(a)             64-node words of a scan level
 //   P::kPiece               edges per queue entry
 //   P::kAdmits              a level may have more members than the one before
+//   P::join_ticks(p, words) how long the first level that needs others waits for them
 //   P::advance(a, sh, nf, mf, scan, record)  wave 0, uniform arguments: the
 //                             next level's plan from the sums over the
 //                             workgroups (set_plan)
@@ -177,6 +178,14 @@ __device__ __forceinline__ void set_plan(SessShared<P>& sh, bool end, bool scan,
     sh.p.fe = (unsigned)fe;
     sh.p.scan = scan ? 1u : 0u;
   }
+}
+
+// How long a level waits for its members, where later levels may have more: at least
+// kJoinTicks, and where there is much to do as long as a few would take for part of it
+// (512 edges, or 64 nodes looked at, per 10 ns).
+template <class State>
+__device__ __forceinline__ unsigned long long admit_ticks(const SessPlan<State>& p, int words) {
+  return kJoinTicks + (p.scan ? (unsigned)words : p.fe >> 9);
 }
 
 // Wave 0: segment sizes (lane s holds that of segment s) to LDS.
@@ -780,8 +789,9 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
         if (mode == kModeEnd || mode == kModeSolo) {
         } else if (uniform(sh.p.ranks) == kNoRanks) {
           // the first level that needs others
+          const unsigned long long ticks = P::join_ticks(sh.p, P::words(a));
           bool all = uniform((unsigned)sh.all) != 0;
-          while (!all && wall_clock64() - t_start <= kJoinTicks) all = joined_count(sc) >= gridDim.x;
+          while (!all && wall_clock64() - t_start <= ticks) all = joined_count(sc) >= gridDim.x;
           if (!all) more = sess_admit(sc, sh);
           else if (lane == 0) sh.p.ranks = kLaunchRanks, sh.all = 1;
         } else if (P::kAdmits && !uniform((unsigned)sh.all)) {

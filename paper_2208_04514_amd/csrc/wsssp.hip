@@ -141,6 +141,10 @@ enum WPhase {
 struct WeightPolicy {
   static constexpr int kPiece = kWeightPiece;
   static constexpr bool kAdmits = true;
+  template <class Plan>
+  static __device__ __forceinline__ unsigned long long join_ticks(const Plan& p, int words) {
+    return admit_ticks(p, words);
+  }
   using Args = WArgs;
   struct State {
     unsigned phase, par;        // par: membership bitmap of the frontier
