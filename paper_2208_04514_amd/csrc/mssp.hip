@@ -2175,7 +2175,9 @@ static dawn_status session_enqueue(Ctx* ctx, const GraphRec* g, BatchJob& j) {
   BatchWs* w = j.w;
   hipStream_t s = w->stream;
   if (j.launches > 2) {
-    const int need = std::min(w->nplanes + 2, kMaxPlanes);
+    // (one: a graph keeps its planes, and a budget may have room for no more than the
+    // run's depth takes)
+    const int need = std::min(w->nplanes + 1, kMaxPlanes);
     if (need == w->nplanes)
       return fail(DAWN_E_DEVICE, "batched traversal exceeds %d levels", (1 << kMaxPlanes) - 1);
     DAWN_TRY(batch_ensure_planes(w, need, j.W));
