@@ -24,6 +24,28 @@ dawn_status fail(dawn_status st, const char* fmt, ...) {
 
 void clear_error() { g_err[0] = 0; }
 
+// Light rows that no run is reading go back to the budget; true if there were any.
+static bool drop_light_rows(Ctx* ctx) {
+  std::vector<std::shared_ptr<LightRows>> drop;
+  std::vector<std::shared_ptr<Weights>> held;
+  {
+    std::lock_guard<std::mutex> lk(ctx->rows_mu);
+    for (std::weak_ptr<Weights>& x : ctx->weighted) {
+      std::shared_ptr<Weights> w = x.lock();
+      if (!w) continue;
+      // (a run takes its reference under this lock)
+      if (w->rows && w->rows.use_count() == 1)
+        drop.push_back(std::move(w->rows));
+      else if (w->rows)
+        held.push_back(std::move(w));
+    }
+    ctx->weighted.assign(held.begin(), held.end());
+  }
+  return !drop.empty();
+}
+
+static dawn_status alloc_within_budget(Ctx* ctx, void** p, size_t bytes, bool from_reserve);
+
 dawn_status dev_alloc(Ctx* ctx, void** p, size_t bytes, bool from_reserve) {
   *p = nullptr;
   if (bytes == 0) bytes = 1;
@@ -34,6 +56,15 @@ dawn_status dev_alloc(Ctx* ctx, void** p, size_t bytes, bool from_reserve) {
     ctx->fail_after.fetch_sub(1);
     if (left == 0) return fail(DAWN_E_NO_MEMORY, "device allocation refused (injected failure)");
   }
+  dawn_status s = alloc_within_budget(ctx, p, bytes, from_reserve);
+  if (s == DAWN_E_NO_MEMORY && drop_light_rows(ctx)) {
+    clear_error();
+    s = alloc_within_budget(ctx, p, bytes, from_reserve);
+  }
+  return s;
+}
+
+static dawn_status alloc_within_budget(Ctx* ctx, void** p, size_t bytes, bool from_reserve) {
   std::lock_guard<std::mutex> lk(ctx->budget_mu);
   const uint64_t used = ctx->used.load(), res = ctx->reserved.load();
   if (from_reserve) {
@@ -55,10 +86,14 @@ dawn_status dev_alloc(Ctx* ctx, void** p, size_t bytes, bool from_reserve) {
 }
 
 dawn_status dev_reserve(Ctx* ctx, size_t bytes) {
-  std::lock_guard<std::mutex> lk(ctx->budget_mu);
-  if (ctx->used.load() + ctx->reserved.load() + bytes > ctx->budget)
+  auto fits = [ctx, bytes]() {
+    std::lock_guard<std::mutex> lk(ctx->budget_mu);
+    if (ctx->used.load() + ctx->reserved.load() + bytes > ctx->budget) return false;
+    ctx->reserved += bytes;
+    return true;
+  };
+  if (!fits() && !(drop_light_rows(ctx) && fits()))
     return fail(DAWN_E_NO_MEMORY, "HBM budget exceeded: cannot set aside %zu bytes", bytes);
-  ctx->reserved += bytes;
   return DAWN_OK;
 }
 
@@ -322,6 +357,11 @@ dawn_status dawn_graph_get_info(dawn_ctx* c, int32_t graph, dawn_graph_info* out
   out->zero_out_degree = g->zero_out;
   out->s_wcc = g->wcc_ready ? (int32_t)g->wcc_nodes.size() : -1;
   out->device_bytes = (int64_t)g->bytes;
+  if (g->weights) {
+    std::lock_guard<std::mutex> lr(g->ctx->rows_mu);
+    const LightRows* r = g->weights->rows.get();
+    out->device_bytes += (int64_t)(g->weights->bytes + (r ? 2 * r->edge_bytes + r->node_bytes : 0));
+  }
   return DAWN_OK;
 }
 
@@ -345,31 +385,23 @@ dawn_status dawn_graph_set_weights(dawn_ctx* c, int32_t graph, const int32_t* we
     return fail(DAWN_E_INVALID_ARG, "max weight %d x (n - 1) = %lld exceeds int32 distances", mx,
                 (long long)mx * (g->n - 1));
   DAWN_HIP(hipSetDevice(ctx->device));
-  int32_t* d = nullptr;
+  auto w = std::make_shared<Weights>();
+  w->ctx = ctx;
+  w->max_w = mx;
   const size_t bytes = (size_t)std::max(g->m, 1LL) * 4;
-  DAWN_TRY(dev_alloc(ctx, (void**)&d, bytes));
-  hipError_t e = g->m > 0 ? hipMemcpy(d, weights, (size_t)g->m * 4, hipMemcpyHostToDevice) : hipSuccess;
-  if (e != hipSuccess) {
-    dev_free(ctx, d, bytes);
-    return fail(DAWN_E_DEVICE, "weights upload: %s", hipGetErrorString(e));
+  DAWN_TRY(dev_alloc(ctx, (void**)&w->wt, bytes));
+  w->bytes = bytes;
+  hipError_t e =
+      g->m > 0 ? hipMemcpy(w->wt, weights, (size_t)g->m * 4, hipMemcpyHostToDevice) : hipSuccess;
+  if (e != hipSuccess) return fail(DAWN_E_DEVICE, "weights upload: %s", hipGetErrorString(e));
+  DAWN_TRY(wsssp_layout(ctx, g.get(), g->m > 0 ? (double)sum / (double)g->m : 0.0, w.get()));
+  {
+    std::lock_guard<std::mutex> lk(ctx->rows_mu);
+    if (w->rows) ctx->weighted.push_back(w);
   }
-  WeightRows rows;
-  dawn_status st = wsssp_layout(ctx, g.get(), d, mx, g->m > 0 ? (double)sum / (double)g->m : 0.0,
-                                &rows);
-  if (st != DAWN_OK) {
-    dev_free(ctx, d, bytes);
-    return st;
-  }
+  // (the ones before go with the last run that reads them)
   std::lock_guard<std::mutex> lk(g->mu);
-  g->bytes += bytes * (rows.light ? 3 : 1) + (rows.light ? (size_t)g->n * 4 : 0);
-  if (g->wt) g->bytes -= bytes * (g->w_light ? 3 : 1) + (g->w_light ? (size_t)g->n * 4 : 0);
-  wsssp_weights_free(g.get());
-  g->wt = d;
-  g->max_w = mx;
-  g->w_col = rows.col;
-  g->w_wt = rows.wt;
-  g->w_light = rows.light;
-  g->w_delta = rows.delta;
+  g->weights.swap(w);
   return DAWN_OK;
 }
 

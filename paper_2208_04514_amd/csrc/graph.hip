@@ -247,7 +247,7 @@ GraphRec::~GraphRec() {
   if (stage) dev_free(ctx, stage, stage_bytes);
   stage = nullptr;
   wsssp_pool_free(this);
-  wsssp_weights_free(this);
+  weights.reset();
   wcc_sub.reset();
   if (ctx) free_graph_buffers(this);
 }

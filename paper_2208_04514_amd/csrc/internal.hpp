@@ -312,6 +312,25 @@ struct SsspWs {
   ~SsspWs();
 };
 
+// The rows of a weighted graph with the edges lighter than its bucket width first, and
+// how many those are.  Runs do without: a refused allocation takes them back.
+struct LightRows {
+  Ctx* ctx = nullptr;
+  int32_t *col = nullptr, *wt = nullptr, *light = nullptr;
+  size_t edge_bytes = 0, node_bytes = 0;
+  ~LightRows();
+};
+// A graph's weights (wsssp.hip), held by the graph and by the runs that use them.
+struct Weights {
+  Ctx* ctx = nullptr;
+  int32_t* wt = nullptr;                  // of each CSR entry
+  size_t bytes = 0;
+  int32_t max_w = 0;
+  int32_t delta = 1;                      // bucket width
+  std::shared_ptr<LightRows> rows;        // guarded by Ctx::rows_mu
+  ~Weights();
+};
+
 struct BatchWs;   // batched traversal buffers (mssp.hip)
 void batch_ws_destroy(BatchWs* ws);
 
@@ -347,15 +366,7 @@ struct GraphRec {
   std::mutex mu;                          // guards the pools and the WCC cache
   std::vector<std::unique_ptr<SsspWs>> sssp_pool;
   std::vector<BatchWs*> batch_pool;
-  // weighted graphs (dawn_graph_set_weights): weight of each CSR entry
-  int32_t* wt = nullptr;
-  int32_t max_w = 0;
-  // the rows with the edges lighter than w_delta first, and how many those are
-  // (null: no such copy)
-  int32_t* w_col = nullptr;
-  int32_t* w_wt = nullptr;
-  int32_t* w_light = nullptr;
-  int32_t w_delta = 1;
+  std::shared_ptr<Weights> weights;       // dawn_graph_set_weights (null: none)
   void* wpool = nullptr;                  // pooled weighted-run workspaces (wsssp.hip)
   // device staging of host-destination batched rows, kept between calls
   int32_t* stage = nullptr;
@@ -394,6 +405,8 @@ struct Ctx {
   std::atomic<int> callers{0};
   std::atomic<uint64_t> crowd_ns[3] = {};
   std::atomic<uint64_t> queued_ns{0};
+  std::mutex rows_mu;
+  std::vector<std::weak_ptr<Weights>> weighted;   // those that may have LightRows
   // streams of the single-source calls (StreamLease)
   std::mutex stream_mu;
   struct {
@@ -480,14 +493,8 @@ dawn_status sssp_run_noalloc(Ctx* ctx, GraphRec* g, const dawn_params& p, int32_
 dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool device_out,
                       dawn_run_stats* stats);
 void wsssp_pool_free(GraphRec* g);
-// Bucket width for these weights and the rows laid out for it (device).
-struct WeightRows {
-  int32_t delta;
-  int32_t *col, *wt, *light;
-};
-dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, int32_t* wt, int32_t max_w, double mean_w,
-                         WeightRows* out);
-void wsssp_weights_free(GraphRec* g);
+// Bucket width for the weights w and the rows laid out for it.
+dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, double mean_w, Weights* w);
 
 // mssp.hip
 dawn_status mssp_run(Ctx* ctx, GraphRec* g, const dawn_params& p, const int32_t* sources,

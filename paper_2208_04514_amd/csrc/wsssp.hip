@@ -684,55 +684,56 @@ void wsssp_pool_free(GraphRec* g) {
   g->wpool = nullptr;
 }
 
-void wsssp_weights_free(GraphRec* g) {
-  Ctx* ctx = g->ctx;
-  const size_t mb = (size_t)std::max(g->m, 1LL) * 4;
-  if (g->wt) dev_free(ctx, g->wt, mb);
-  if (g->w_light) {
-    dev_free(ctx, g->w_col, mb);
-    dev_free(ctx, g->w_wt, mb);
-    dev_free(ctx, g->w_light, (size_t)g->n * 4);
-  }
-  g->wt = g->w_col = g->w_wt = g->w_light = nullptr;
+LightRows::~LightRows() {
+  dev_free(ctx, col, edge_bytes);
+  dev_free(ctx, wt, edge_bytes);
+  dev_free(ctx, light, node_bytes);
 }
 
-dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, int32_t* wt, int32_t max_w, double mean_w,
-                         WeightRows* out) {
+Weights::~Weights() { dev_free(ctx, wt, bytes); }
+
+dawn_status wsssp_layout(Ctx* ctx, GraphRec* g, double mean_w, Weights* w) {
   const double mean_deg = std::max((double)g->m / (double)g->n, 1.0);
   double delta = kDelta * mean_w / mean_deg;
-  if (delta >= (double)max_w) delta = kDeltaWhole * mean_w / mean_deg;
-  out->delta = (int32_t)std::min(std::max(delta, 1.0), 1e9);
-  out->col = out->wt = out->light = nullptr;
-  if (out->delta >= max_w || g->m == 0) return DAWN_OK;
+  if (delta >= (double)w->max_w) delta = kDeltaWhole * mean_w / mean_deg;
+  w->delta = (int32_t)std::min(std::max(delta, 1.0), 1e9);
+  if (w->delta >= w->max_w || g->m == 0) return DAWN_OK;
   const size_t mb = (size_t)g->m * 4, nb = (size_t)g->n * 4;
-  // only out of plenty: the copy must not take the room of what has none other
+  // only out of plenty
   const uint64_t used = ctx->used.load() + ctx->reserved.load();
   if (used > ctx->budget || 2 * mb + nb > (ctx->budget - used) / 8) return DAWN_OK;
-  if (dev_alloc(ctx, (void**)&out->col, mb) != DAWN_OK ||
-      dev_alloc(ctx, (void**)&out->wt, mb) != DAWN_OK ||
-      dev_alloc(ctx, (void**)&out->light, nb) != DAWN_OK) {
+  auto r = std::make_shared<LightRows>();
+  r->ctx = ctx;
+  r->edge_bytes = mb;
+  r->node_bytes = nb;
+  if (dev_alloc(ctx, (void**)&r->col, mb) != DAWN_OK ||
+      dev_alloc(ctx, (void**)&r->wt, mb) != DAWN_OK ||
+      dev_alloc(ctx, (void**)&r->light, nb) != DAWN_OK) {
     // no room for the copy: near rounds then look at whole rows
     clear_error();
-    if (out->col) dev_free(ctx, out->col, mb);
-    if (out->wt) dev_free(ctx, out->wt, mb);
-    out->col = out->wt = out->light = nullptr;
     return DAWN_OK;
   }
-  hipLaunchKernelGGL(split_rows, dim3(ctx->num_cu * 4), dim3(kSB), 0, 0, g->n, g->rp, g->col, wt,
-                     out->delta, out->col, out->wt, out->light);
+  hipLaunchKernelGGL(split_rows, dim3(ctx->num_cu * 4), dim3(kSB), 0, 0, g->n, g->rp, g->col, w->wt,
+                     w->delta, r->col, r->wt, r->light);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return fail(DAWN_E_DEVICE, "weights layout: %s", hipGetErrorString(e));
+  w->rows = std::move(r);
   return DAWN_OK;
 }
 
 dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool device_out,
                       dawn_run_stats* stats) {
   const uint64_t t0 = now_ns();
-  if (!g->wt) return fail(DAWN_E_INVALID_ARG, "graph %d has no weights (dawn_graph_set_weights)", g->id);
+  // (held to the end of the run, which reads them: another call may replace them)
+  std::shared_ptr<Weights> weights;
+  std::shared_ptr<LightRows> rows;
   std::unique_ptr<WWs> w;
   {
     std::lock_guard<std::mutex> lk(g->mu);
+    weights = g->weights;
+    if (!weights)
+      return fail(DAWN_E_INVALID_ARG, "graph %d has no weights (dawn_graph_set_weights)", g->id);
     WsspPool* pool = reinterpret_cast<WsspPool*>(g->wpool);
     if (pool && !pool->ws.empty()) {
       w = std::move(pool->ws.back());
@@ -761,15 +762,16 @@ dawn_status wsssp_run(Ctx* ctx, GraphRec* g, int32_t source, int32_t* dist, bool
   a.fin = w->fin;
   a.half = (unsigned)(g->m / 2);
   {
-    std::lock_guard<std::mutex> lk(g->mu);
-    a.wt = g->wt;
-    a.delta = (unsigned)g->w_delta;
-    a.split = g->w_delta < g->max_w ? 1 : 0;
-    if (a.split && g->w_light) {
-      a.col = g->w_col;
-      a.wt = g->w_wt;
-      a.light = g->w_light;
-    }
+    std::lock_guard<std::mutex> lk(ctx->rows_mu);
+    rows = weights->rows;
+  }
+  a.wt = weights->wt;
+  a.delta = (unsigned)weights->delta;
+  a.split = weights->delta < weights->max_w ? 1 : 0;
+  if (rows) {
+    a.col = rows->col;
+    a.wt = rows->wt;
+    a.light = rows->light;
   }
   // Every bucket but an empty last one holds a reached node that no earlier one held
   // (distances past a bucket are lowered to no less than its end), so there are at most

@@ -29,3 +29,39 @@ def test_planes_for_the_depth_alone(dawn_lib):
         # (a run looks one level past its last)
         planes = max(3, int(levels).bit_length())
         assert used[levels] - used[6] == (planes - 3) * n * 8, levels
+
+
+def test_second_copy_of_weighted_rows_makes_way(dawn_lib):
+    """What a budget held without the second copy of a weighted graph's rows it holds
+    with it: an allocation that does not fit takes the copy back."""
+    ctx = D.dawn_create(0, 64 << 20)
+    try:
+        g = gg.gen_rmat(13, 16, 4)
+        w = gg.gen_weights(g, 1, 100, seed=3, symmetric=True)
+        src = int(np.argmax(g.out_degree()))
+        want = oracle.wsssp(g, w, src)
+        h = D.dawn_graph_upload(ctx, g.row_ptr, g.col)
+        plain = D.dawn_graph_get_info(ctx, h)["device_bytes"]
+        D.dawn_graph_set_weights(ctx, h, w)
+        copy = D.dawn_graph_get_info(ctx, h)["device_bytes"] - plain - 4 * g.m
+        assert copy > 8 * g.m                             # the budget is plenty for it
+        got, _ = D.dawn_sssp_weighted(ctx, h, src)
+        assert np.array_equal(got.astype(np.int64), want)
+        used, budget = D.dawn_memory(ctx)
+        n = 2000                                          # a graph that fits without the copy
+        m = (budget - used + copy // 2) // 8
+        rng = np.random.default_rng(1)
+        rp = np.linspace(0, m, n + 1).astype(np.int32)
+        h2 = D.dawn_graph_upload(ctx, rp, rng.integers(0, n, int(rp[-1])).astype(np.int32))
+        assert D.dawn_graph_get_info(ctx, h)["device_bytes"] == plain + 4 * g.m
+        for _ in range(2):
+            got, st = D.dawn_sssp_weighted(ctx, h, src)
+            assert np.array_equal(got.astype(np.int64), want)
+            assert st["reached"] == (want >= 0).sum()
+        D.dawn_graph_release(ctx, h2)
+        D.dawn_graph_set_weights(ctx, h, w)               # and it is made again
+        assert D.dawn_graph_get_info(ctx, h)["device_bytes"] == plain + 4 * g.m + copy
+        got, _ = D.dawn_sssp_weighted(ctx, h, src)
+        assert np.array_equal(got.astype(np.int64), want)
+    finally:
+        D.dawn_destroy(ctx)
