@@ -531,6 +531,7 @@ static dawn_status launch_t(Ctx* ctx, const BatchArgs& a, FusedCtrl* fc, hipStre
   SessArgs x;
   memset(&x, 0, sizeof(x));
   x.sc = &fc->sess;
+  x.stripes = 1;
   const int grid = sess_grid(ctx, std::min(occ, kSessPerCu), ctx_share(ctx, false),
                              std::max((a.n + 63) / 64 * P + a.npc, kSessGroup * kSW), 0);
   hipLaunchKernelGGL(batch_session<P>, dim3(grid), dim3(kSB), 0, s, b, x);

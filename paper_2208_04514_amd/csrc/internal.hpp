@@ -230,11 +230,11 @@ struct SessCtrl {
 };
 struct SessArgs {
   SessCtrl* sc;
-  // frontier entries (row start, degree) by queue parity.  Grid levels:
-  // kSessStripes sub-queues of qcap entries; cluster levels: kSessGroup
+  // frontier entries (row start, degree) by queue parity.  Grid levels: `stripes`
+  // sub-queues (at most kSessStripes) of qcap entries; cluster levels: kSessGroup
   // segments of ccap entries, then one of all the rest
   u64* q[2];
-  unsigned qcap, ccap;
+  unsigned qcap, ccap, stripes;
   int32_t source;
 };
 // A level's rows cut into pieces of `piece` edges: at most one partial piece per
@@ -249,10 +249,11 @@ inline size_t sess_queue_cap(int32_t n, long long m, int piece) {
 // weighted rounds always do (R-MAT 20 x 4: 10.2 ms with 256, 5.7 with 64).
 constexpr int kHopPiece = 1024;
 constexpr int kWeightPiece = 64;
-// A cluster segment: the segments together take at most 7 of the 8 sub-queues'
-// room, so that the rest holds any level's entries.
-inline size_t sess_cluster_cap(size_t qcap) {
-  const size_t fit = (kSessStripes - 1) * qcap / kSessGroup;
+// A cluster segment: with `stripes` sub-queues the segments together take at most the
+// room of all but one, so that the rest holds any level's entries.  (With a single one
+// there are none, and every entry goes to the common segment.)
+inline size_t sess_cluster_cap(size_t qcap, int stripes) {
+  const size_t fit = (size_t)(stripes - 1) * qcap / kSessGroup;
   return fit < 2048 ? fit : 2048;
 }
 

@@ -511,7 +511,7 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
   const int t = threadIdx.x, lane = lane_id();
   SessCtrl* sc = x.sc;
   SessSlot* slot = &sc->slot[gen % 3];
-  const unsigned stripe = sh.rank % kSessStripes;
+  const unsigned stripe = sh.rank % x.stripes;
   u64* qout = x.q[sh.p.qp ^ 1] + (size_t)stripe * x.qcap;
   unsigned* qn = &slot->q[stripe].n;
   const bool scans = P::scans(sh.p);

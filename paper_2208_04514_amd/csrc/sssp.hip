@@ -1360,6 +1360,14 @@ SsspWs::~SsspWs() {
   if (ev1) hipEventDestroy(ev1);
 }
 
+static size_t level_queue_bytes(int32_t n) { return (size_t)kStripes * n * 4 + 256; }
+// A session's sub-queues: as many as there is room for in the level kernel's queues
+// (one, where a graph of a few nodes has very many edges).
+static int hop_stripes(int32_t n, long long m) {
+  const size_t fit = level_queue_bytes(n) / (sess_queue_cap(n, m, kHopPiece) * 8);
+  return fit >= (size_t)kSessStripes ? kSessStripes : 1;
+}
+
 static dawn_status ws_create(Ctx* ctx, GraphRec* g, hipStream_t stream,
                              std::unique_ptr<SsspWs>* out) {
   std::unique_ptr<SsspWs> w(new SsspWs());
@@ -1385,8 +1393,8 @@ static dawn_status ws_create(Ctx* ctx, GraphRec* g, hipStream_t stream,
     if ((s = alloc((void**)&w->vis[i], nw * 8 + 256)) != DAWN_OK) break;
     // (the level kernel's sub-queues, or a session's)
     if ((s = alloc((void**)&w->qs[i],
-                   std::max((size_t)kStripes * n * 4 + 256,
-                            (size_t)kSessStripes * sess_queue_cap(n, g->m, kHopPiece) * 8))) != DAWN_OK)
+                   std::max(level_queue_bytes(n),
+                            hop_stripes(n, g->m) * sess_queue_cap(n, g->m, kHopPiece) * 8))) != DAWN_OK)
       break;
     if ((s = alloc((void**)&w->cu[i], chunk_cap * 4)) != DAWN_OK) break;
     if ((s = alloc((void**)&w->ck[i], chunk_cap * 4)) != DAWN_OK) break;
@@ -1532,7 +1540,8 @@ static dawn_status run_session(Ctx* ctx, SsspWs* w, const SsspArgs& a0, int bloc
   x.q[0] = reinterpret_cast<u64*>(w->qs[0]);
   x.q[1] = reinterpret_cast<u64*>(w->qs[1]);
   x.qcap = (unsigned)sess_queue_cap(a.n, a.m, kHopPiece);
-  x.ccap = (unsigned)sess_cluster_cap(x.qcap);
+  x.stripes = (unsigned)hop_stripes(a.n, a.m);
+  x.ccap = (unsigned)sess_cluster_cap(x.qcap, (int)x.stripes);
   x.source = source;
   DAWN_TRY(sess_launch(ctx, a, x, blocks_per_cu, w->stream));
   DAWN_HIP(hipEventRecord(w->ev1, w->stream));

@@ -100,13 +100,14 @@ static std::vector<int> search(const Graph& g, int s, bool weighted) {
 struct Queues {
   std::vector<u64> q[2];
   SessArgs x{};
-  Queues(const Graph& g, int piece, SessCtrl* sc, int s) {
+  Queues(const Graph& g, int piece, SessCtrl* sc, int s, int stripes) {
     x.qcap = (unsigned)sess_queue_cap(g.n, (long long)g.col.size() - 1, piece);
-    x.ccap = (unsigned)sess_cluster_cap(x.qcap);
+    x.stripes = (unsigned)stripes;
+    x.ccap = (unsigned)sess_cluster_cap(x.qcap, stripes);
     x.sc = sc;
     x.source = s;
     for (int i = 0; i < 2; ++i) {
-      q[i].assign((size_t)kSessStripes * x.qcap, ~0ull - 5);     // (no entry stands for a row)
+      q[i].assign((size_t)stripes * x.qcap, ~0ull - 5);     // (no entry stands for a row)
       x.q[i] = q[i].data();
     }
   }
@@ -163,6 +164,7 @@ static const char* batch(const Graph& g, int k, emu::Launch l, bool stall) {
   SessArgs x;
   memset((void*)&x, 0, sizeof(x));
   x.sc = &fc->sess;
+  x.stripes = 1;
   for (int run = 0;; ++run) {
     for (int i = 0; i < (stall && run == 1 ? 4 : 1); ++i) planes.emplace_back(vis.size(), 0ull);
     b.nplanes = (int)planes.size();
@@ -237,7 +239,7 @@ int main(int argc, char** argv) {
   std::map<std::string, double> o{{"grid", 40}, {"hold", 0}, {"held", 0}, {"late", 0},
                                   {"levels", 60}, {"wide", 120}, {"small", 6}, {"wmax", 40},
                                   {"ticks", 0.02}, {"mode", 3}, {"path", 0}, {"k", 40}, {"stall", 0},
-                                  {"join", 0}, {"after", 400000}};
+                                  {"join", 0}, {"after", 400000}, {"stripes", kSessStripes}};
   for (int i = 4; i < argc; ++i) {
     const std::string a = argv[i];
     const size_t eq = a.find('=');
@@ -298,7 +300,7 @@ int main(int argc, char** argv) {
       a.mode = (int)o["mode"], a.alpha = 14, a.beta = 24, a.lane_edges = 4;
       a.small_edges = (int)o["small"];
       a.level_nf = level_nf.data(), a.level_dir = dir.data(), a.lrec = g.n + 1;
-      Queues q(g, kHopPiece, sc.get(), s);
+      Queues q(g, kHopPiece, sc.get(), s, (int)o["stripes"]);
       std::vector<std::unique_ptr<HopPolicy::Shared>> sh(l.grid);
       for (auto& p : sh) p.reset(new HopPolicy::Shared());
       const unsigned long long used =
@@ -337,7 +339,7 @@ int main(int argc, char** argv) {
       }
       a.half = (unsigned)(m / 2);
       a.max_rounds = (unsigned)(4 * g.n + 4);
-      Queues q(g, kWeightPiece, &ctrl->sess, s);
+      Queues q(g, kWeightPiece, &ctrl->sess, s, (int)o["stripes"]);
       std::vector<std::unique_ptr<WeightPolicy::Shared>> sh(l.grid);
       for (auto& p : sh) p.reset(new WeightPolicy::Shared()), p->low = 0;
       const unsigned long long used =

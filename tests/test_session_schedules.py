@@ -96,3 +96,8 @@ def test_late_workgroups_take_part(emu, kind):
 
 def test_callers_share_the_device(emu):
     emu("callers", 0, 1, jobs=1)
+
+
+@pytest.mark.parametrize("kind", ["hop", "weighted"])
+def test_one_queue(emu, kind):
+    emu(kind, 1, 4, stripes=1)

@@ -65,3 +65,30 @@ def test_second_copy_of_weighted_rows_makes_way(dawn_lib):
         assert np.array_equal(got.astype(np.int64), want)
     finally:
         D.dawn_destroy(ctx)
+
+
+def test_dense_weighted_graph_with_one_queue(dawn_lib):
+    """A dense graph's weighted run where the session's four sub-queues do not fit:
+    it runs with one, in the memory that a launch per round took."""
+    n, m = 2000, 1_000_000
+    rng = np.random.default_rng(4)
+    rp = np.linspace(0, m, n + 1).astype(np.int32)
+    g = gg.Graph(n, rp, rng.integers(0, n, m).astype(np.int32))
+    w = rng.integers(1, 101, m).astype(np.int32)
+    ctx = D.dawn_create(0, 0)
+    try:
+        D.dawn_graph_upload(ctx, g.row_ptr, g.col)
+        used = D.dawn_memory(ctx)[0]
+    finally:
+        D.dawn_destroy(ctx)
+    ctx = D.dawn_create(0, used + 4 * m + 128 * n + 5 * m // 16)
+    try:
+        h = D.dawn_graph_upload(ctx, g.row_ptr, g.col)
+        D.dawn_graph_set_weights(ctx, h, w)
+        for s in (0, 77, n - 1):
+            got, st = D.dawn_sssp_weighted(ctx, h, s)
+            want = oracle.wsssp(g, w, s)
+            assert np.array_equal(got.astype(np.int64), want)
+            assert st["reached"] == (want >= 0).sum()
+    finally:
+        D.dawn_destroy(ctx)
