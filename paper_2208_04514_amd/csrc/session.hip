@@ -369,7 +369,9 @@ dawn_status sess_launch(Ctx* ctx, const SsspArgs& a, const SessArgs& x, int bloc
   }
   const int per_cu = std::min(blocks_per_cu > 0 ? blocks_per_cu : kSessPerCu, occ);
   const int grid = sess_grid(ctx, per_cu, blocks_per_cu > 0 ? 1 : ctx_share(ctx), a.nw, a.m);
-  const int fill = std::max(1, std::min((a.n + kSB - 1) / kSB, ctx->num_cu * 4));
+  // (the control block in one go)
+  constexpr int least = (int)((sizeof(SessCtrl) / 8 + kSB - 1) / kSB);
+  const int fill = std::max(least, std::min((a.n + kSB - 1) / kSB, ctx->num_cu * 4));
   hipLaunchKernelGGL(sess_init, dim3(fill), dim3(kSB), 0, s, a, x);
   hipLaunchKernelGGL(sssp_session, dim3(grid), dim3(kSB), 0, s, a, x);
   hipLaunchKernelGGL(sess_close, dim3(1), dim3(kWave), 0, s, a);

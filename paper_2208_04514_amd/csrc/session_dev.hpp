@@ -503,8 +503,8 @@ __device__ __forceinline__ void walk_rows(int* own, unsigned ngroups, unsigned g
 }
 
 // ---------------------------------------------------------------- grid level --
-// Runs the level, then the barrier.  Returns the next record's number (0: a
-// wait timed out).
+// Runs the level, then the barrier.  Returns the next record's number, or in
+// workgroup 0 this one's if the next is still to be published (0: a wait timed out).
 template <class P>
 __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const SessArgs& x,
                                                SessShared<P>& sh, unsigned gen) {
@@ -563,7 +563,6 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
         }
       }
       if (ok) {
-        if (P::kAdmits && !uniform((unsigned)sh.all)) sess_admit(sc, sh);
         const unsigned sq = lane < kSessStripes ? ld_relaxed(&slot->q[lane].n) : 0u;
         constexpr u64 low = (1ull << 48) - 1;
         const u64 nf = wave_sum(w0 & low), mf = wave_sum(w1 & low);
@@ -574,8 +573,11 @@ __device__ __forceinline__ unsigned grid_level(const typename P::Args& a, const 
           sh.p.qp ^= 1;
           sh.p.stride = x.qcap;
         }
-        sess_publish(sc, sh, gen + 1);
-        next = gen + 1;
+        next = gen;
+        if (!P::kAdmits || uniform((unsigned)sh.all)) {
+          sess_publish(sc, sh, gen + 1);
+          next = gen + 1;
+        }
       }
     } else {
       next = sess_poll(sc, sh, gen, false);
@@ -785,20 +787,18 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
     if (lead) {
       if (t < kWave) {
         const unsigned mode = uniform(sh.p.mode);
-        bool more = false;
-        if (mode == kModeEnd || mode == kModeSolo) {
-        } else if (uniform(sh.p.ranks) == kNoRanks) {
+        const bool wide = mode == kModeGrid || mode == kModeCluster;
+        const bool first = wide && uniform(sh.p.ranks) == kNoRanks;
+        bool all = uniform((unsigned)sh.all) != 0;
+        if (first) {
           // the first level that needs others
           const unsigned long long ticks = P::join_ticks(sh.p, P::words(a));
-          bool all = uniform((unsigned)sh.all) != 0;
           while (!all && wall_clock64() - t_start <= ticks) all = joined_count(sc) >= gridDim.x;
-          if (!all) more = sess_admit(sc, sh);
-          else if (lane == 0) sh.p.ranks = kLaunchRanks, sh.all = 1;
-        } else if (P::kAdmits && !uniform((unsigned)sh.all)) {
-          more = sess_admit(sc, sh);
+          if (all && lane == 0) sh.p.ranks = kLaunchRanks, sh.all = 1;
         }
-        // the plan was made for other members
-        if (more) set_plan<P>(sh, false, sh.p.scan != 0, uniform(sh.p.fe), P::words(a), 0);
+        // (if more get in, the plan was made for other members)
+        if (wide && !all && (first || P::kAdmits) && sess_admit(sc, sh))
+          set_plan<P>(sh, false, sh.p.scan != 0, uniform(sh.p.fe), P::words(a), 0);
         sess_publish(sc, sh, gen + 1);
       }
       gen += 1;
@@ -819,8 +819,10 @@ __device__ __forceinline__ void session(const typename P::Args& a, const SessArg
     const bool mine = sh.p.mode == kModeSolo ? bid == 0 : ranked && sh.rank < sh.p.K;
     bool poll = !mine;
     if (mine && sh.p.mode == kModeGrid) {
-      gen = grid_level(a, x, sh, gen);
-      if (!gen) return;
+      const unsigned next = grid_level(a, x, sh, gen);
+      if (!next) return;
+      lead = next == gen;
+      gen = next;
     } else if (mine) {
       if (sh.p.mode == kModeCluster) {
         if (!cluster_run(a, x, sh)) return;
