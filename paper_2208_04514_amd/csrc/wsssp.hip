@@ -134,7 +134,9 @@ enum WPhase {
   kNear = 0,        // relax the frontier's rows; targets below the bound join the next
   kSettled = 1,     // collect the bucket's nodes
   kHeavy = 2,       // relax their edges that reach the bound or past it
-  kCollect = 3      // collect the nodes of the next bucket
+  // from here on the smallest distance past the bucket may be wanted
+  kCollect = 3,     // collect the nodes of the next bucket
+  kHeavyGap = 4     // kHeavy, where no node was less than delta past the bucket
 };
 
 // Queue entries are (node, piece of its row).
@@ -260,9 +262,9 @@ struct WeightPolicy {
 
   template <int E, class Src, class Sink>
   static __device__ __forceinline__ void push(const WArgs& a, int* own, const State& u,
-                                              unsigned ngroups, unsigned gw, unsigned nwaves,
+                                              unsigned phase, unsigned ngroups, unsigned gw, unsigned nwaves,
                                               const Src& src, Sink& sink, SessCount& c) {
-    const bool near = uniform(u.phase) == kNear;
+    const bool near = phase == kNear;
     const unsigned hi = uniform(u.hi);
     const unsigned par = uniform(u.par);
     u64* mine = par ? a.inq[1] : a.inq[0];
@@ -343,10 +345,6 @@ struct WeightPolicy {
     }
   }
 
-  // The levels that may have to find the smallest distance past the bucket.
-  static __device__ __forceinline__ bool wants_low(const State& u) {
-    return u.phase == kCollect || (u.phase == kHeavy && u.gap);
-  }
   static __device__ __forceinline__ void wave_low(S& base, const SessCount& c) {
     if (__ballot(c.scan != 0)) return;      // not to be asked for
     const int x = __builtin_amdgcn_readlane(wave_incl_max(c.low), kWave - 1);
@@ -356,8 +354,9 @@ struct WeightPolicy {
   template <class Sink>
   static __device__ __forceinline__ void step(const WArgs& a, const SessArgs& x, S& sh,
                                               Sink& sink, SessCount& c) {
-    level(a, x, sh, sink, c);
-    if (!wants_low(sh.p.u)) return;
+    const unsigned phase = uniform(sh.p.u.phase);
+    level(a, x, sh, phase, sink, c);
+    if (phase < kCollect) return;
     wave_low(sh, c);
     __syncthreads();
     const unsigned k = uniform(sh.p.u.lows);
@@ -377,31 +376,32 @@ struct WeightPolicy {
 
   template <class Sink>
   static __device__ __forceinline__ void level(const WArgs& a, const SessArgs& x, S& sh,
-                                               Sink& sink, SessCount& c) {
+                                               unsigned phase, Sink& sink, SessCount& c) {
     const int wv = threadIdx.x / kWave;
     const unsigned K = uniform(sh.p.K);
     const unsigned nwaves = K * kSW;
     const unsigned gw = (unsigned)wv * K + sh.rank;
     const State& u = sh.p.u;
     if (uniform(sh.p.scan)) {
-      collect(a, uniform(u.phase) == kSettled, lite_rows(a, u), uniform(u.lo), uniform(u.hi), gw, nwaves, sink, c);
+      collect(a, phase == kSettled, lite_rows(a, u), uniform(u.lo), uniform(u.hi), gw, nwaves, sink, c);
       return;
     }
     const QueueSrc<WeightPolicy> src = queue_src(sh, x.q[sh.p.qp]);
     const unsigned ngroups = uniform(sh.pre_g[kSessSegs]);
     if (uniform(sh.p.fe) <= nwaves * 2 * kWave)
-      push<1>(a, sh.own[wv], u, ngroups, gw, nwaves, src, sink, c);
+      push<1>(a, sh.own[wv], u, phase, ngroups, gw, nwaves, src, sink, c);
     else
-      push<4>(a, sh.own[wv], u, ngroups, gw, nwaves, src, sink, c);
+      push<4>(a, sh.own[wv], u, phase, ngroups, gw, nwaves, src, sink, c);
   }
 
   template <class Sink>
   static __device__ __forceinline__ void solo(const WArgs& a, S& sh, const u64* cur,
                                               unsigned ncur, Sink& sink, SessCount& c) {
     const int wv = threadIdx.x / kWave;
-    push<1>(a, sh.own[wv], sh.p.u, (ncur + kWave - 1) / kWave, (unsigned)wv, (unsigned)kSW,
+    const unsigned phase = uniform(sh.p.u.phase);
+    push<1>(a, sh.own[wv], sh.p.u, phase, (ncur + kWave - 1) / kWave, (unsigned)wv, (unsigned)kSW,
             ListSrc{cur, ncur}, sink, c);
-    if (wants_low(sh.p.u)) wave_low(sh, c);
+    if (phase >= kCollect) wave_low(sh, c);
   }
 
   // What follows the level just run, from the rows it put in the queue (nf, of
@@ -413,7 +413,7 @@ struct WeightPolicy {
     unsigned done = 0;
     u.steps += 1;
     unsigned low = 0;
-    if (wants_low(u)) {
+    if (u.phase >= kCollect) {
       if (sh.p.mode == kModeSolo) {
         low = (unsigned)static_cast<Shared&>(sh).low;
       } else {
@@ -441,11 +441,12 @@ struct WeightPolicy {
       case kSettled:
         // (nobody with an edge: what lies past the bucket is as it was)
         if (nf)
-          u.phase = kHeavy;
+          u.phase = u.gap ? kHeavyGap : kHeavy;
         else
           done = next_bucket(u, u.width);
         break;
       case kHeavy:
+      case kHeavyGap:
         // (with a gap, the smallest of what lay past it before and what this level made)
         u.far = max(u.far, low);
         // past the bulk of the edges, and on long stretches of next to none, buckets
