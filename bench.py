@@ -424,19 +424,20 @@ GRID_MEDIUM = dict(medium_edges=16384, medium_groups=32, blocks_per_cu=0)
 def grid_bench(D, ctx, k_src=16):
     """The damaged 2048^2 grid (about 120 levels) under each level-loop
     driver, and the no-shortcut grid (thousands of levels) under two; driver
-    3 also with medium push levels run on a few workgroups per launch."""
+    4 also with medium push levels run on a few workgroups per launch (driver
+    3, all levels in one launch, has no such knob)."""
     import torch
     import graphgen as gg
     res = {}
-    for name, drivers, ks in (("grid2048", (1, 2, 3, 4, "3m"), k_src), ("grid2048ns", (1, 3, "3m"), 1)):
+    for name, drivers, ks in (("grid2048", (1, 2, 3, 4, "4m"), k_src), ("grid2048ns", (1, 3, "4m"), 1)):
         g, src = gg.load_config(name)
         h = D.dawn_graph_upload(ctx, g.row_ptr, g.col)
         out = torch.empty(g.n, dtype=torch.int32, device="cuda")
         entry = {}
         for drv in drivers:
-            kw = dict(driver=3 if drv == "3m" else drv, graph_levels=32, blocks_per_cu=1,
-                      medium_edges=0)
-            if drv == "3m":
+            kw = dict(driver=4 if drv == "4m" else drv, graph_levels=32,
+                      blocks_per_cu=0 if drv == 3 else 1, medium_edges=0)
+            if drv == "4m":
                 kw.update(GRID_MEDIUM)
             D.dawn_set_params(ctx, h, **kw)
             D.dawn_sssp(ctx, h, int(src[0]), out=out)
@@ -448,7 +449,7 @@ def grid_bench(D, ctx, k_src=16):
                 lv.append(st["levels"])
             torch.cuda.synchronize()
             t = time.perf_counter() - t0
-            entry["driver3_medium" if drv == "3m" else f"driver{drv}"] = {
+            entry["driver4_medium" if drv == "4m" else f"driver{drv}"] = {
                 "ms_per_source": round(t / ks * 1e3, 3), "gteps": round(se / t / 1e9, 3),
                 "us_per_level": round(t / sum(lv) * 1e6, 2), "levels": lv}
         res[name] = entry
