@@ -478,7 +478,9 @@ __device__ __forceinline__ void walk_rows(int* own, unsigned ngroups, unsigned g
     const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
     const int excl = incl - deg;
     const int first = rs - excl;      // edge x of the union is entry first + x
-    for (int eb = (int)part * E * kWave; eb < total; eb += (int)split * E * kWave) {
+    const int step = (int)split * E * kWave;
+    int eb = (int)part * E * kWave;
+    while (eb < total) {
 #pragma unroll
       for (int q = 0; q < E; ++q) own[q * kWave + lane] = 0;
       wave_sync();
@@ -498,6 +500,9 @@ __device__ __forceinline__ void walk_rows(int* own, unsigned ngroups, unsigned g
       }
       wave_sync();      // the marks are read before the next step clears them
       edges(o, at, has);
+      // (eb + step may be past 2^31: a source's row is one entry, however long)
+      if (total - eb <= step) break;
+      eb += step;
     }
   }
 }

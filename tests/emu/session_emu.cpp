@@ -197,6 +197,45 @@ static const char* batch(const Graph& g, int k, emu::Launch l, bool stall) {
   return reached == fc->part[0].reached ? nullptr : "totals";
 }
 
+// A row of nearly 2^31 edges, as the last wave of the largest launch walks it.
+static const char* walk() {
+  const int start = 7, deg = 0x7fffffff - 64;
+  unsigned long long seen = 0, mine = 0;
+  bool out = false;
+  std::vector<int> own(4 * kWave);
+  const unsigned nwaves = kSessGroups * kSessGroup * 8;
+  struct {
+    u64 get(unsigned, int lane) const { return lane ? kNoEntry : 1ull; }
+  } src;
+  emu::Launch l;
+  l.grid = 1;
+  l.block = 64;
+  l.limit = 1000000;
+  const unsigned long long used = emu::run(l, [&](unsigned) {
+    walk_rows<4>(
+        own.data(), 1, nwaves - 1, nwaves, src,
+        [&](u64 e, unsigned, int& rs, int& d) {
+          if (e == kNoEntry) return;
+          rs = start;
+          d = deg;
+        },
+        [&](const int* o, const int* at, const bool* has) {
+          for (int q = 0; q < 4; ++q)
+            if (has[q]) {
+              ++seen;
+              out = out || o[q] != 0 || at[q] < start || at[q] - start >= deg;
+            }
+        });
+  });
+  const unsigned long long step = 2ull * nwaves * 256;       // two shares a wave
+  for (unsigned long long part : {(unsigned long long)nwaves - 1, 2ull * nwaves - 1})
+    for (unsigned long long e = part * 256; e < (unsigned long long)deg; e += step)
+      mine += std::min<unsigned long long>(256, (unsigned long long)deg - e);
+  if (!used) return "no end";
+  if (out) return "an edge outside the row";
+  return seen == mine ? nullptr : "edges";
+}
+
 // The part of the device that a call's session may take.
 static const char* callers() {
   Ctx c;
@@ -230,8 +269,8 @@ static const char* callers() {
 
 int main(int argc, char** argv) {
   const std::string kind = argv[1];
-  if (kind == "callers") {
-    const char* e = callers();
+  if (kind == "callers" || kind == "walk") {
+    const char* e = kind == "walk" ? walk() : callers();
     return e ? failed(e, 0) : 0;
   }
   const unsigned long long seed0 = strtoull(argv[2], nullptr, 10);

@@ -101,3 +101,7 @@ def test_callers_share_the_device(emu):
 @pytest.mark.parametrize("kind", ["hop", "weighted"])
 def test_one_queue(emu, kind):
     emu(kind, 1, 4, stripes=1)
+
+
+def test_row_of_nearly_two_to_the_31(emu):
+    emu("walk", 0, 1, jobs=1)
