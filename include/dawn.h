@@ -29,8 +29,9 @@
  *    and no copy to the host is made.
  *  - Synchronous calls (everything except dawn_serve_submit and
  *    dawn_mssp_device) have finished writing their outputs when they return.
- *  - All calls are thread-safe on one context.  Calls on the same graph from
- *    several threads run on separate HIP streams.
+ *  - All calls are thread-safe on one context.  Calls from several threads run
+ *    on separate HIP streams (single-source ones on up to four), and those in
+ *    flight at a time take a part of the device each.
  */
 #ifndef DAWN_H
 #define DAWN_H
@@ -103,10 +104,10 @@ typedef struct dawn_params {
   int32_t driver;             /* 1 persistent cooperative kernel (grid barrier per level),
                                  2 one launch per level with a host read-back,
                                  3 (default) one launch that runs every level, each on as many
-                                   workgroups as it can use (one; the first 32; all that
-                                   started), between an init launch and one that reports the
-                                   end to host memory; `block`, `big_degree`, `graph_levels`
-                                   and the medium_* knobs do not apply to it,
+                                   workgroups as it can use (one; the first 32; all that have
+                                   started by then), between an init launch and one that
+                                   reports the end to host memory; `block`, `big_degree`,
+                                   `graph_levels` and the medium_* knobs do not apply to it,
                                  4 level launches captured once in a HIP graph and replayed,
                                    `graph_levels` per host check */
   int32_t direction;          /* 1 push only, 2 pull only, 3 switch by alpha/beta */
@@ -114,7 +115,7 @@ typedef struct dawn_params {
   int32_t blocks_per_cu;      /* workgroups per compute unit of the persistent kernel, of driver
                                  3's launch and of level launches (0: as many as a compute unit
                                  holds; driver 3's then has no more than a level of the graph
-                                 can use; level
+                                 can use, divided by the calls that share the device; level
                                  launches then use no more workgroups than a pull level has
                                  visited-bitmap words for, and at least one per compute unit) */
   int32_t big_degree;         /* push: out-degree at which a node's edges are spread over the grid */
@@ -214,10 +215,11 @@ dawn_status dawn_graph_get_info(dawn_ctx *ctx, int32_t graph, dawn_graph_info *o
 /* Attach non-negative integer edge weights to a resident graph (copied:
  * weights[e], host, m int32, belongs to CSR entry e, the edge from e's row to
  * col[e]; with room to spare in the budget a second copy of the rows is kept,
- * ordered for the rounds).  A second call replaces them.  Every path length must fit an int32
- * distance: max weight x (n - 1) <= 2^31 - 2.  Used by dawn_sssp_weighted
- * only.  Errors: INVALID_ARG (null, negative or too large weights),
- * NOT_FOUND, NO_MEMORY, DEVICE. */
+ * ordered for the rounds, until an allocation wants its room).  A second call
+ * replaces them; runs in flight keep the ones they started with.  Every path
+ * length must fit an int32 distance: max weight x (n - 1) <= 2^31 - 2.  Used by
+ * dawn_sssp_weighted only.  Errors: INVALID_ARG (null, negative or too large
+ * weights), NOT_FOUND, NO_MEMORY, DEVICE. */
 dawn_status dawn_graph_set_weights(dawn_ctx *ctx, int32_t graph, const int32_t *weights);
 
 /* Tuning knobs (see dawn_params).  set: fields left 0 keep the default;

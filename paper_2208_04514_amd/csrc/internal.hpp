@@ -356,8 +356,8 @@ struct GraphRec {
   size_t pc_cap = 0;
   int32_t max_out_deg = 0;
   int32_t zero_out = 0;
-  // level launches the recent traversals needed (the direct-launch driver
-  // queues about this many before its first host check)
+  // level launches the recent traversals needed (the no-allocation variant queues
+  // about this many before its first host check)
   std::atomic<int> launch_hint{0};
   // batched level loop: levels the last run launched before it saw the end
   // (its expansions + 1), the size of the next run's first chunk

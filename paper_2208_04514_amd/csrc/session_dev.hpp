@@ -48,14 +48,14 @@
 // Membership.  A barrier may only count workgroups that are running, and a
 // plain launch promises nothing about that.  So each workgroup joins with an
 // atomic when it starts; workgroup 0 gives ranks to those that have, when the
-// first level that needs others comes up (after a short wait), and to later ones
-// ahead of each level: beside other work on the device few may start with the
-// launch.  (Two callers on R-MAT 20, weighted: with the first list kept for the whole
-// run one call in 20 took 50 ms instead of 2.)  A rank is kept for good, so that
-// whoever is behind still belongs where it did.  Every
-// wait is on workgroups that have joined, hence on running ones, and is
-// bounded besides.  The bound is on a wait for the next record, so a long run of
-// solo or cluster levels publishes one now and then.
+// first level that needs others comes up (after a wait of P::join_ticks), and to
+// later ones ahead of each level: beside other work on the device few may start
+// with the launch.  (Two callers on R-MAT 20, weighted: with the first list kept for
+// the whole run one call in 20 took 50 ms instead of 2.)  A rank is kept for good,
+// so that whoever is behind still belongs where it did.  Every wait is on workgroups
+// that have joined, hence on running ones, and is bounded besides.  The bound is on
+// a wait for the next record, so a long run of solo or cluster levels publishes one
+// now and then.
 #pragma once
 
 #include <algorithm>
