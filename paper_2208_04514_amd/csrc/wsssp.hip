@@ -27,8 +27,8 @@
 // a bitmap, which most targets of the later pass are found in (it stays in the
 // caches; distances at random do not).  No bucket is empty, however far apart distances
 // lie, so the levels are bounded by the nodes (max_rounds): a collection counts the
-// nodes less than delta past its bucket, and where there is none the next bucket starts
-// at the smallest distance further on, or that the relaxations past T make.
+// nodes less than delta past its bucket, and where there is none the next bucket is the
+// one with the smallest distance further on, or that the relaxations past T make.
 //
 // delta = kDelta x mean weight / mean out-degree: the denser the graph, the
 // more often an unsettled node's row is relaxed in vain, the sparser, the fewer
@@ -37,7 +37,7 @@
 // Bound: on R-MAT 20 the rounds over hubs' rows (random distances, several
 // dependent accesses an edge: 30 to 120 G edges/s), on grids the levels' chains
 // (5 to 8 us each).  Per source (MI355X, weights 1..100), hop order with a
-// launch per round -> now: R-MAT 20 1.78 -> 1.13 ms, grid 1024^2 4.6 -> 1.7 ms.
+// launch per round -> now: R-MAT 20 1.74 -> 1.00 ms, grid 1024^2 4.6 -> 1.7 ms.
 //
 // Distances are int32 with -1 for "unreached": compared as unsigned, -1 is
 // the largest value, so the atomic minimum needs no sentinel pass.  The
@@ -153,7 +153,7 @@ struct WeightPolicy {
     unsigned lo, hi;            // the bucket: distances in [lo, hi)
     unsigned width;             // of the next collection
     unsigned rounds;            // near rounds run
-    unsigned far;               // kFar - the next bucket's start (0: none)
+    unsigned far;               // kFar - a bound below the next distance (0: none left)
     unsigned gap;               // no node was less than delta past the bucket
     unsigned lows;              // levels that used WCtrl::low so far
     unsigned settled;           // out-edges of the finished buckets
@@ -217,13 +217,24 @@ struct WeightPolicy {
       }
       put(first, v[0], deg, sink, c);
     } else {
+      if (!near) {
+        // (whether another relaxation got there first is not asked: its candidate is the
+        // smaller then, and the minimum the same.  R-MAT 20's heavy levels take 331 us a
+        // source with atomics that return the old distance, 295 so)
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          if (has[i] && cand[i] < cur[i]) {
+            umin_atomic(&a.dist[v[i]], cand[i]);
+            c.low = max(c.low, kFar - (int)cand[i]);
+          }
+        }
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < E; ++i) {
         go[i] = false;
         if (has[i] && cand[i] < cur[i]) go[i] = cand[i] < umin_atomic(&a.dist[v[i]], cand[i]);
-        if (go[i] && !near) c.low = max(c.low, kFar - (int)cand[i]);
       }
-      if (!near) return;
       bool first[E];
       int deg[E];
 #pragma unroll
@@ -435,7 +446,7 @@ struct WeightPolicy {
         } else {
           // (no edge is longer than the bucket: the next holds a node, or none is left)
           u.far = (unsigned)kFar - u.hi;
-          done = next_bucket(u, a.delta);
+          done = next_bucket(u, a.delta, a.delta);
         }
         break;
       case kSettled:
@@ -443,7 +454,7 @@ struct WeightPolicy {
         if (nf)
           u.phase = u.gap ? kHeavyGap : kHeavy;
         else
-          done = next_bucket(u, u.width);
+          done = next_bucket(u, a.delta, u.width);
         break;
       case kHeavy:
       case kHeavyGap:
@@ -453,9 +464,10 @@ struct WeightPolicy {
         // of little work: fewer, wider ones
         u.settled += sh.p.fe;
         u.thin = sh.p.fe <= (unsigned)kSoloCap ? u.thin + 1 : 0;
-        done = next_bucket(u, (sh.p.fe < kSmallBucket && u.settled > a.half) || u.thin > kThinBuckets
-                                  ? min(u.width * 2, 1u << 30)
-                                  : a.delta);
+        done = next_bucket(u, a.delta,
+                           (sh.p.fe < kSmallBucket && u.settled > a.half) || u.thin > kThinBuckets
+                               ? min(u.width * 2, 1u << 30)
+                               : a.delta);
         break;
       default:
         u.gap = close == 0;
@@ -465,7 +477,7 @@ struct WeightPolicy {
         else if (a.split)
           u.phase = kSettled;       // its nodes have heavy edges, or none
         else
-          done = next_bucket(u, u.width);
+          done = next_bucket(u, a.delta, u.width);
     }
     if (u.steps > a.max_rounds) done = 2;
     set_plan<WeightPolicy>(sh, done != 0, u.phase == kSettled || u.phase == kCollect, mf, a.nw,
@@ -479,11 +491,13 @@ struct WeightPolicy {
       }
     }
   }
-  // The bucket that starts at the smallest distance left; 1 if there is none.
-  static __device__ __forceinline__ unsigned next_bucket(State& u, unsigned width) {
+  // The bucket with the smallest distance left, a whole number of deltas behind this one
+  // (R-MAT 20, 8 sources: 7.95 ms, with buckets that start at that distance 8.93: where they
+  // begin then depends on the source's lightest edges; width is no less than delta); 1 if there is none.
+  static __device__ __forceinline__ unsigned next_bucket(State& u, unsigned delta, unsigned width) {
     if (!u.far) return 1;
     u.phase = kCollect;
-    u.lo = (unsigned)kFar - u.far;
+    u.lo = u.hi + ((unsigned)kFar - u.far - u.hi) / delta * delta;
     u.width = width;
     u.hi = min(u.lo + width, (unsigned)kFar);
     return 0;

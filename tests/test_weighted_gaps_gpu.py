@@ -64,3 +64,18 @@ def test_heavy_tails(ctx, name, top):
     rng = np.random.default_rng(top)
     w = np.exp(rng.random(g.m) ** 3 * np.log(top)).astype(np.int32)
     _run(ctx, g, w, [0, 4, int(np.argmax(g.out_degree())), g.n - 1])
+
+
+@pytest.mark.parametrize("first", [101, 117, 133])
+def test_gap_ends_anywhere_in_a_bucket(ctx, first):
+    """The next distance lies at the start, in the middle or at the end of the bucket that
+    is skipped to: steps of 16 consecutive lengths, with buckets some 12 wide."""
+    path, clique = 24, 60
+    a, b = np.nonzero(np.triu(np.ones((clique, clique), bool), 1))
+    pairs = np.concatenate([np.stack([np.arange(path), np.arange(1, path + 1)], 1),
+                            path + np.stack([a, b], 1)])
+    g = gg.gen_edges(path + clique, pairs, symmetrize=True)
+    light = np.random.default_rng(first).integers(1, 61, g.m)
+    for weight in range(first, first + 16):
+        heavy = _weights(g, path, weight)
+        _run(ctx, g, np.where(heavy > 1, heavy, light).astype(np.int32), [0, path // 2, g.n - 1])
